@@ -58,6 +58,23 @@ __device__ __forceinline__ const WorkUnit& unit_for_block(const WorkUnit* units,
   return units[(i % kNumXcd) * per_xcd + i / kNumXcd];
 }
 
+// As unit_for_block when each unit is shared by PARTS workgroups of `rows`
+// rows each: they follow one another on the unit's die.  `reverse` hands the
+// last rows out first (causal query tiles: the part with the most keys).
+// rows == 0 in the result: nothing to do.
+template <int PARTS>
+__device__ __forceinline__ WorkUnit part_for_block(const WorkUnit* units, int per_xcd, int rows, bool reverse) {
+  const int i = blockIdx.x, pos = i / kNumXcd;
+  WorkUnit u = units[(i % kNumXcd) * per_xcd + pos / PARTS];
+  if constexpr (PARTS > 1) {
+    const int part = pos % PARTS;
+    const int off = (reverse ? PARTS - 1 - part : part) * rows;
+    u.row0 += off;
+    u.rows = uint16_t(max(0, min(rows, int(u.rows) - off)));
+  }
+  return u;
+}
+
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -313,5 +330,27 @@ struct DmaVecPair {
   }
 };
 
+// Sums over the streams of a workgroup.  KS streams (wavefronts that walked
+// different keys, or queries, for the same group of rows) each hold a partial
+// accumulator of NP four-register pieces; stream x % KS adds up piece x.  The
+// others hand theirs over through LDS (1 KB per piece, lane-major 16-byte
+// slots: no bank conflicts), the pieces of the first KS / 2 owners in `lo`,
+// the rest in `hi` (HALF_BYTES each).  The caller puts a barrier between the
+// puts and the gets and adds in stream order, so that the sum does not depend
+// on who adds.
+template <int NP, int GROUPS, int KS>
+struct StreamSum {
+  static constexpr int PPO = (NP + KS - 1) / KS;  // pieces per owner, at most
+  static constexpr int HALF_BYTES = KS > 1 ? GROUPS * (KS / 2) * PPO * (KS - 1) * 1024 : 0;
+  DCP_LDS char* lo;
+  DCP_LDS char* hi;
+  int group, lane;
+  // piece x of stream t (t != x % KS)
+  __device__ __forceinline__ DCP_LDS f32x4* slot(int x, int t) const {
+    const int o = x % KS, half = KS / 2;
+    const int n = ((group * half + o % half) * PPO + x / KS) * (KS - 1) + (t > o ? t - 1 : t);
+    return (DCP_LDS f32x4*)((o < half ? lo : hi) + n * 1024 + lane * 16);
+  }
+};
 
 }  // namespace dcp

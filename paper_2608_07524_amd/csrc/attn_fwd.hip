@@ -33,6 +33,17 @@
 // against the initial m overflow) takes its row max, moves m and forms its
 // weights again.
 // Epilogue: O = O^T / l (bf16), LSE = (m + log2 l) * ln 2.
+//
+// Few tiles (KS > 1): a batch whose tiles leave CUs idle -- one sequence of a
+// few heads -- is bound by the length of one workgroup's walk over its keys.
+// Each tile is then cut into parts (tile_parts) and the NW wavefronts of a
+// workgroup form KS key streams x NW / KS query groups: stream s takes every
+// KS-th share of the keys, so the walk is KS times shorter, and the streams'
+// (m, l, O) are merged through LDS at the end, in stream order.  No scratch
+// memory and no second launch.  Two heads of width 128: 4,096 tokens 103 ->
+// 47 us, 16,384 tokens 390 -> 274 us (128 tiles on 256 CUs; with every CU busy
+// the clock drops, and the 128k shard's rate would give 237); width 72, 4,096
+// tokens 79 -> 32 us.
 #include <type_traits>
 
 #include "attn_common.h"
@@ -45,6 +56,7 @@ constexpr int kFwdBN = 64;
 // Ring depth: tile kt + kFwdStages - 1 streams in while tile kt is consumed.
 constexpr int kFwdStages = 4;
 static_assert(kFwdStages >= 3 && kWinFwdStages >= 3, "tiles kt and kt + 1 are read while kt + 2 lands");
+constexpr int kFwdSplitStages = 6;  // with key streams (a step takes two tiles)
 constexpr float kRescaleSlack = 8.0f;  // log2 units
 constexpr float kNoMax = -1e30f;       // running max before any key
 constexpr float kSumBound = 256.0f;    // 2^kRescaleSlack
@@ -75,7 +87,7 @@ struct FwdShape {
   static constexpr int VSKEW = PV16 ? 16 : 0;
 };
 
-template <int D, int NW, bool CAUSAL, bool PACKED, int STAGES>
+template <int D, int NW, bool CAUSAL, bool PACKED, int STAGES, int KS>
 __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const __bf16* __restrict__ q,
                                                            const __bf16* __restrict__ k,
                                                            const __bf16* __restrict__ v, __bf16* __restrict__ o,
@@ -98,8 +110,11 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const __bf16* __restr
 
   __shared__ __attribute__((aligned(16))) __bf16 Ks[NST * KBUF];
   __shared__ __attribute__((aligned(16))) __bf16 Vs[NST * VBUF];
+  static_assert(KS == 1 || (!PACKED && KS % 2 == 0 && NW % KS == 0), "key streams: sequence tiles, whole ring tiles per step");
+  constexpr int QG = NW / KS;  // 32-query groups of the workgroup
+  __shared__ float ML[KS > 1 ? NW * 64 : 1];  // each wavefront's (m, l) per query
 
-  const WorkUnit u = unit_for_block(units, per_xcd);
+  WorkUnit u = part_for_block<PACKED ? 1 : kFwdWaves * KS / NW>(units, per_xcd, 32 * QG, CAUSAL);
   if (u.rows == 0) return;
   const int h = u.head;
   const int tid = threadIdx.x;
@@ -118,7 +133,9 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const __bf16* __restr
   const __bf16* v_pad = S::ONES_ROW ? consts + kConstOnes : zero;
 
   const int tile_q0 = u.row0 - u.seq0;  // first query of the tile, sequence-relative
-  const int wave_q0 = tile_q0 + wave * 32;
+  const int qw = KS > 1 ? wave % QG : wave;        // this wavefront's query group
+  const int stream = KS > 1 ? wave / QG : 0;       // and key stream
+  const int wave_q0 = tile_q0 + qw * 32;
   constexpr bool packed = PACKED;  // a list of packed windows only
   const int seqlen = packed ? int(u.rows) : u.seqlen;  // (window-relative offsets when packed)
   const int qi = wave_q0 + j;  // this lane's query
@@ -132,7 +149,7 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const __bf16* __restr
 #pragma unroll
   for (int kd = 0; kd < NKD; ++kd) {
     const int col = 16 * kd + 8 * g;
-    if (wave * 32 + j < u.rows && col < D) {
+    if (qw * 32 + j < u.rows && col < D) {
       qf[kd] = *reinterpret_cast<const bf16x8*>(qh + int64_t(qi) * ts + col);
     } else {
       qf[kd] = bf16x8{};
@@ -156,8 +173,8 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const __bf16* __restr
   // (the last tile of a sequence) only copies and idles.  In a packed
   // window every block is masked, and the wavefront first idles through
   // the tiles before its first query's sequence (t_first).
-  const bool live = wave * 32 < u.rows;
-  const int last = min(31, int(u.rows) - 1 - wave * 32);  // lane of the wavefront's last query
+  const bool live = qw * 32 < u.rows;
+  const int last = min(31, int(u.rows) - 1 - qw * 32);  // lane of the wavefront's last query
   const int wave_keys = packed ? min(__builtin_amdgcn_readlane(k_hi, max(last, 0)), CAUSAL ? wave_q0 + 32 : seqlen)
                                : (CAUSAL ? min(seqlen, wave_q0 + 32) : seqlen);
   const int t_first = packed && live ? __builtin_amdgcn_readfirstlane(k_lo) / BN : 0;
@@ -300,6 +317,43 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const __bf16* __restr
     for (int db = 0; db < NDB; ++db) oacc[db] *= alpha;
   };
 
+  // P = exp2(S*scale*log2e - m) as bf16 (B operand of the PV product)
+  auto form_weights = [&](const f32x16& s, bf16x8 (&pb)[2]) DCP_INLINE {
+    auto exps = [&]() DCP_INLINE {
+      const float mneg = -m_use;
+#pragma unroll
+      for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pb[hh][e] = __bf16(__builtin_amdgcn_exp2f(fmaf(s[8 * hh + e], scale_log2, mneg)));
+    };
+    exps();
+    if constexpr (!S::ONES_ROW) {
+      // the row sum over the same bf16 weights the PV product uses, so that
+      // O = sum_j w_j v_j / sum_j w_j is an exact weighted mean of V rows
+      // (pairwise dot products with (1, 1), one accumulator per half)
+      auto psum = [&]() DCP_INLINE {
+        const bf16x2 one = {__bf16(1.f), __bf16(1.f)};
+        float lh[2] = {0.f, 0.f};
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            lh[hh] = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pb[hh][2 * i], pb[hh][2 * i + 1]}, one, lh[hh], false);
+        return lh[0] + lh[1];
+      };
+      // The lane's 16 weights sum to at most 2^8 unless one of them may
+      // exceed 2^8 (or overflowed): only then is the block's row max taken,
+      // m moved to it and the weights formed again (at most 1 each).
+      float ls = psum();
+      if (__builtin_amdgcn_ballot_w64(!(ls <= kSumBound))) {
+        move_max(row_max(s));
+        exps();
+        ls = psum();
+      }
+      l_run += ls;
+    }
+  };
+
   // O^T += V^T P^T for the current block (V rows at vcur, this lane's
   // transposing-read offset included).  32x32 blocks: A = V^T rows
   // 32db + (lane % 32) over keys 16hh + 4g + {0..3, 8..11}, B = pb[hh]
@@ -335,6 +389,213 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const __bf16* __restr
         }
     }
   };
+
+  if constexpr (KS > 1) {
+    // A step is BPS 32-key blocks of every stream, G ring tiles in all.  At
+    // step i a wavefront finishes its blocks of step i while forming the
+    // scores up to its first block of step i + 1, so the K tiles run one step
+    // ahead of the V tiles: K of step i + 1 + P and V of step i + P are copied
+    // while step i is processed, P = NSS - 1, into the slots whose last
+    // readers met the barrier before it.  (Two streams take two blocks per
+    // step: at 16,384 tokens 270 us against 300 with one; four have ring
+    // space for one.)
+    constexpr int BPS = KS == 2 ? 2 : 1;
+    constexpr int G = KS * BPS / 2, NSS = NST / G, P = NSS - 1;
+    static_assert(NSS >= 2, "two steps of ring tiles");
+    constexpr int NIS = G * NI;  // copies per wavefront per step
+    static_assert(P * NIS < 64, "vmcnt range");
+    const int n_steps = (key_end + G * BN - 1) / (G * BN);
+    auto issue_k = [&](int i) DCP_INLINE {
+      if (i >= n_steps) return;
+#pragma unroll
+      for (int t = 0; t < G; ++t) {
+        const int k0 = (i * G + t) * BN, valid = min(BN, seqlen - k0);
+        __bf16* dst = &Ks[((unsigned(i) % NSS) * G + t) * KBUF];
+        if (valid == BN)
+          DK::issue_full(dst, kh + int64_t(k0) * ts, fo_k, wave);
+        else
+          DK::issue(dst, kh + int64_t(k0) * ts, ts, valid, zero, zero, wave, lane);
+      }
+    };
+    auto issue_v = [&](int i) DCP_INLINE {
+      if (i >= n_steps) return;
+#pragma unroll
+      for (int t = 0; t < G; ++t) {
+        const int k0 = (i * G + t) * BN, valid = min(BN, seqlen - k0);
+        __bf16* dst = &Vs[((unsigned(i) % NSS) * G + t) * VBUF];
+        if (valid != BN)
+          DV::issue(dst, vh + int64_t(k0) * ts, ts, valid, zero, v_pad, wave, lane);
+        else if constexpr (S::ONES_ROW)
+          DV::issue_full_skip(dst, vh + int64_t(k0) * ts, fo_v, vskip, wave);
+        else
+          DV::issue_full(dst, vh + int64_t(k0) * ts, fo_v, wave);
+      }
+    };
+    // This wavefront's blocks of step i are SB * i + b0 + {0 .. BPS - 1}, the
+    // first of them in half hb of the step's ring tile tb.
+    constexpr int SB = 2 * G;
+    const int b0 = BPS * stream;
+    const unsigned tb = unsigned(b0) >> 1, hb = unsigned(b0) & 1;
+    auto k_at = [&](int i) DCP_INLINE {
+      unsigned a = ((unsigned(i) % NSS) * G + tb) * KBUF + hb * 32 * KSTR + kr_off;
+      asm("" : "+v"(a));
+      return a;
+    };
+    auto v_at = [&](int i) DCP_INLINE {
+      unsigned a = ((unsigned(i) % NSS) * G + tb) * VBUF + hb * (32 * VSTR + 2 * S::VSKEW) + tr_lane;
+      asm("" : "+v"(a));
+      return a;
+    };
+    issue_k(0);
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      issue_k(i + 1);
+      issue_v(i);
+    }
+    if (n_steps > P)
+      wait_vmcnt<P * NIS>();
+    else
+      wait_vmcnt<0>();
+    __syncthreads();
+    // steps with a block of this wavefront's keys (b < nb), and the leading
+    // ones whose successor blocks are all unmasked
+    const int n_mine = nb > b0 ? (nb - b0 + SB - 1) / SB : 0;
+    const int n_plain = max(0, (b_mask - b0 - BPS) / SB);  // SB * (i + 1) + b0 + BPS <= b_mask
+    f32x16 sc{};
+    bf16x8 kn[NKD];
+    if (n_mine > 0) {
+      const unsigned ka = k_at(0);
+      load_k(ka, kn);
+      sc = scores(kn);
+      if constexpr (BPS == 2) load_k(ka + 32 * KSTR, kn);
+      if (b_mask <= b0) apply_mask(sc, b0);
+      rescale(row_max(sc), true);
+    }
+    auto wait_step = [&](int i) DCP_INLINE {  // before step i: K of step i + 1 and V of step i
+      if (i + P < n_steps)
+        wait_vmcnt<(P - 1) * NIS>();
+      else
+        wait_vmcnt<0>();
+      __syncthreads();
+    };
+    wait_step(0);
+    // One block: its weights and its share of O (V rows at vcur) while the
+    // scores of the wavefront's next block bn (fragments in kn) are formed;
+    // with two blocks per step kn then takes the fragments at kafter.
+    auto block = [&](int bn, unsigned kafter, unsigned vcur, auto mask_tag) DCP_INLINE {
+      constexpr bool MASK = decltype(mask_tag)::value;
+      f32x16 sn = scores(kn);
+      if constexpr (BPS == 2) load_k(kafter, kn);
+      bf16x8 pb[2];
+      form_weights(sc, pb);
+      if constexpr (MASK) apply_mask(sn, bn);
+      pv_product(pb, vcur);
+      if constexpr (S::ONES_ROW) rescale(row_max(sn), !MASK || bn < nb);
+      sc = sn;
+    };
+    auto step = [&](int i, auto mask_tag) DCP_INLINE {
+      issue_k(i + 1 + P);
+      issue_v(i + P);
+      const unsigned ka = k_at(i + 1), va = v_at(i);
+      if constexpr (BPS == 2) {
+        block(SB * i + b0 + 1, ka, va, mask_tag);
+        block(SB * (i + 1) + b0, ka + 32 * KSTR, va + 32 * VSTR + 2 * S::VSKEW, mask_tag);
+      } else {
+        load_k(ka, kn);
+        block(SB * (i + 1) + b0, 0, va, mask_tag);
+      }
+      wait_step(i + 1);
+    };
+    int i = 0;
+    for (; i < n_plain; ++i) step(i, std::false_type{});
+    for (; i < n_mine; ++i) step(i, std::true_type{});
+    for (; i < n_steps; ++i) {
+      issue_k(i + 1 + P);
+      issue_v(i + P);
+      wait_step(i + 1);
+    }
+
+    // Combine the streams.  With m_t, l_t, acc_t the stream t's running max,
+    // row sum and accumulator of a query and M = max_t m_t:
+    //   O = sum_t w_t acc_t,  w_t = exp2(m_t - M) / sum_t l_t exp2(m_t - M)
+    // (a stream without keys of the query has m = kNoMax, l = 0: weight 0).
+    // The accumulators are exchanged through the idle ring.
+    constexpr int NP = S::PV16 ? 2 * NMB : 4 * NDB;
+    auto piece = [&](int x) DCP_INLINE {
+      if constexpr (S::PV16) return oacc16[x >> 1][x & 1];
+      return f32x4{oacc[x >> 2][4 * (x & 3)], oacc[x >> 2][4 * (x & 3) + 1], oacc[x >> 2][4 * (x & 3) + 2],
+                   oacc[x >> 2][4 * (x & 3) + 3]};
+    };
+    using Sum = StreamSum<NP, QG, KS>;
+    static_assert(Sum::HALF_BYTES <= NST * KBUF * 2 && Sum::HALF_BYTES <= NST * VBUF * 2, "pieces fit the ring");
+    const Sum sum{(DCP_LDS char*)lds_ptr(Ks), (DCP_LDS char*)lds_ptr(Vs), qw, lane};
+#pragma unroll
+    for (int x = 0; x < NP; ++x)
+      if (x % KS != stream) *sum.slot(x, stream) = piece(x);
+    float l_mine;
+    if constexpr (S::PV16) {
+      constexpr int rg = (D % 16) / 4, rr = D % 4;
+      const int src = 16 * rg + (lane & 15);
+      const float l0 = __shfl(oacc16[NMB - 1][0][rr], src), l1 = __shfl(oacc16[NMB - 1][1][rr], src);
+      l_mine = (j & 16) ? l1 : l0;
+    } else {
+      static_assert(S::PV16 || !S::ONES_ROW, "32-row blocks with a row-sum row have no split form");
+      l_mine = half_swap_sum(l_run);
+    }
+    if (g == 0) {
+      ML[wave * 64 + j] = m_use;
+      ML[wave * 64 + 32 + j] = l_mine;
+    }
+    __syncthreads();
+    // weights of this lane's query (PV16: of queries n and 16 + n)
+    constexpr int NQ = S::PV16 ? 2 : 1;
+    float w[NQ][KS], m_all[NQ], l_all[NQ];
+#pragma unroll
+    for (int c = 0; c < NQ; ++c) {
+      const int qq = S::PV16 ? 16 * c + (lane & 15) : j;
+      m_all[c] = kNoMax;
+#pragma unroll
+      for (int t = 0; t < KS; ++t) m_all[c] = fmaxf(m_all[c], ML[(t * QG + qw) * 64 + qq]);
+      l_all[c] = 0.f;
+#pragma unroll
+      for (int t = 0; t < KS; ++t) {
+        w[c][t] = __builtin_amdgcn_exp2f(ML[(t * QG + qw) * 64 + qq] - m_all[c]);
+        l_all[c] = fmaf(ML[(t * QG + qw) * 64 + 32 + qq], w[c][t], l_all[c]);
+      }
+      const float inv = 1.f / l_all[c];
+#pragma unroll
+      for (int t = 0; t < KS; ++t) w[c][t] *= inv;
+    }
+#pragma unroll
+    for (int x = 0; x < NP; ++x) {
+      if (x % KS != stream) continue;
+      const int c = S::PV16 ? (x & 1) : 0;
+      const int qrel = 32 * qw + (S::PV16 ? 16 * (x & 1) + (lane & 15) : j);
+      const int d0 = S::PV16 ? 16 * (x >> 1) + 4 * g4 : 32 * (x >> 2) + 8 * (x & 3) + 4 * g;
+      f32x4 acc = {};
+#pragma unroll
+      for (int t = 0; t < KS; ++t) {
+        const f32x4 a = t == stream ? piece(x) : *sum.slot(x, t);
+        acc += a * w[c][t];
+      }
+      if (qrel < u.rows && d0 < D) {
+        bf16x4 r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = __bf16(acc[e]);
+        *reinterpret_cast<bf16x4*>(o + (int64_t(u.row0) + qrel) * ts + int64_t(h) * D + d0) = r;
+      }
+    }
+    if (stream == 0) {
+      const int c = S::PV16 ? (lane & 15) : j;  // (PV16: lane group 0 takes queries n and 16 + n)
+#pragma unroll
+      for (int e = 0; e < NQ; ++e) {
+        const int qrel = 32 * qw + 16 * e + c;
+        if ((S::PV16 ? g4 == 0 : g == 0) && qrel < u.rows)
+          lse[int64_t(h) * T + u.row0 + qrel] = (m_all[e] + __log2f(l_all[e])) * kLn2;
+      }
+    }
+    return;
+  }
 
 #pragma unroll
   for (int t = 0; t < PD; ++t)
@@ -373,41 +634,8 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const __bf16* __restr
     constexpr bool MASK = decltype(mask_tag)::value;
     f32x16 sn = scores(kn);
     load_k(kafter, kn);
-    // P = exp2(S*scale*log2e - m) as bf16 (B operand of the PV product)
     bf16x8 pb[2];
-    auto exps = [&]() DCP_INLINE {
-      const float mneg = -m_use;
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) pb[hh][e] = __bf16(__builtin_amdgcn_exp2f(fmaf(sc[8 * hh + e], scale_log2, mneg)));
-    };
-    exps();
-    if constexpr (!S::ONES_ROW) {
-      // the row sum over the same bf16 weights the PV product uses, so that
-      // O = sum_j w_j v_j / sum_j w_j is an exact weighted mean of V rows
-      // (pairwise dot products with (1, 1), one accumulator per half)
-      auto psum = [&]() DCP_INLINE {
-        const bf16x2 one = {__bf16(1.f), __bf16(1.f)};
-        float lh[2] = {0.f, 0.f};
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            lh[hh] = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pb[hh][2 * i], pb[hh][2 * i + 1]}, one, lh[hh], false);
-        return lh[0] + lh[1];
-      };
-      // The lane's 16 weights sum to at most 2^8 unless one of them may
-      // exceed 2^8 (or overflowed): only then is the block's row max taken,
-      // m moved to it and the weights formed again (at most 1 each).
-      float ls = psum();
-      if (__builtin_amdgcn_ballot_w64(!(ls <= kSumBound))) {
-        move_max(row_max(sc));
-        exps();
-        ls = psum();
-      }
-      l_run += ls;
-    }
+    form_weights(sc, pb);
     if constexpr (MASK) apply_mask(sn, bn);
     pv_product(pb, vcur);
     if constexpr (S::ONES_ROW) rescale(row_max(sn), valid_next);
@@ -496,9 +724,12 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const __bf16* __restr
   }
 }
 
-template <int D, int NW, bool CAUSAL, bool PACKED, int STAGES>
+// NW wavefronts per workgroup in KS key streams: each unit of a sequence-tile
+// list becomes kFwdWaves * KS / NW workgroups.
+template <int D, int NW, bool CAUSAL, bool PACKED, int STAGES, int KS = 1>
 hipError_t launch_fwd_list(const FwdArgs& a, const WorkUnit* units, int n_units) {
-  hipLaunchKernelGGL((attn_fwd_kernel<D, NW, CAUSAL, PACKED, STAGES>), dim3(n_units), dim3(64 * NW), 0, a.stream,
+  constexpr int PARTS = PACKED ? 1 : kFwdWaves * KS / NW;
+  hipLaunchKernelGGL((attn_fwd_kernel<D, NW, CAUSAL, PACKED, STAGES, KS>), dim3(n_units * PARTS), dim3(64 * NW), 0, a.stream,
                      static_cast<const __bf16*>(a.q), static_cast<const __bf16*>(a.k),
                      static_cast<const __bf16*>(a.v), static_cast<__bf16*>(a.o), a.lse,
                      static_cast<const __bf16*>(a.consts), units, static_cast<const uint64_t*>(a.window_starts),
@@ -513,7 +744,14 @@ hipError_t launch_fwd_t(const FwdArgs& a) {
   const WorkUnit* units = static_cast<const WorkUnit*>(a.units);
   if (ev.begin) (void)hipEventRecord(ev.begin, a.stream);
   hipError_t e = hipSuccess;
-  if (a.n_units > 0) e = launch_fwd_list<D, NW, CAUSAL, false, kFwdStages>(a, units, a.n_units);
+  if (a.n_units > 0) {
+    switch (tile_parts(a.n_units, CAUSAL)) {
+      case 8: e = launch_fwd_list<D, NW / 2, CAUSAL, false, kFwdSplitStages, 4>(a, units, a.n_units); break;
+      case 4: e = launch_fwd_list<D, NW, CAUSAL, false, kFwdSplitStages, 4>(a, units, a.n_units); break;
+      case 2: e = launch_fwd_list<D, NW, CAUSAL, false, kFwdSplitStages, 2>(a, units, a.n_units); break;
+      default: e = launch_fwd_list<D, NW, CAUSAL, false, kFwdStages>(a, units, a.n_units);
+    }
+  }
   if (e == hipSuccess && a.n_wunits > 0)
     e = launch_fwd_list<D, kWinFwdWaves, CAUSAL, true, kWinFwdStages>(a, units + a.n_units, a.n_wunits);
   if (ev.end) (void)hipEventRecord(ev.end, a.stream);

@@ -26,6 +26,24 @@ static_assert(sizeof(WorkUnit) == 16, "16 bytes per tile");
 constexpr int kWindowWords = 4;  // 64-bit words per window mask: windows hold at most 256 rows
 
 constexpr int kNumXcd = 8;  // MI355X: 8 accelerator dies, each with its own L2
+constexpr int kNumCU = 256;  // and 32 compute units per die
+
+// How many workgroups share one unit of a sequence-tile list of n_units
+// (padding included): 8 / parts of its rows each, the 8 (or, for 8 parts, 4)
+// wavefronts then splitting the other side of the score matrix as well, so a
+// workgroup's walk is `parts` times shorter.  A workgroup takes most of a
+// CU's LDS, so the chip runs one per CU: parts pay as long as they find idle
+// CUs, and cost where they do not (a barrier per shorter step, and every part
+// streams the same rows).  Forward, 2 heads of width 128, 1 / 2 / 4 / 8 parts:
+// 1,000 tokens (32 units) 32 / 21 / 16 / 15 us; 8,192 (64) 197 / 120 / 92 /
+// 167; 16,384 (128) 399 / 270 / 348 / 636; 20,000 (158) 499 / 580.  Causal
+// units hold half the work on average and come longest first, so two rounds
+// of workgroups still fill the chip: 5,003 tokens (40 units) 121 / 75 / 54 /
+// 53; 20,000 (158) 476 / 285 / 288; 32 heads of 3,001 (384) 108 / 110.
+constexpr int tile_parts(int n_units, bool causal) {
+  const int room = causal ? 2 * kNumCU : kNumCU;
+  return n_units <= room / 8 ? 8 : n_units <= room / 4 ? 4 : n_units <= room / 2 ? 2 : 1;
+}
 
 // Offsets (bf16 elements) of the 16-byte constant chunks every attention
 // workspace starts with.

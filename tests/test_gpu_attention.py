@@ -149,6 +149,31 @@ def test_running_max_moves(torch, D, causal, regime):
     _assert_close(got, ref, n, f"running max {regime} D={D} causal={causal}")
 
 
+# Batches of few tiles: each tile is shared by 8, 4 or 2 workgroups whose
+# wavefronts split the keys (forward, dQ) or queries (dK/dV) into streams.  The
+# head count moves a batch across the rule (256 units for one part each, twice
+# that when causal); lengths leave whole parts, a stream's first or last blocks,
+# or all but one row of the last part empty.
+@pytest.mark.parametrize("D", [64, 72, 128])
+@pytest.mark.parametrize("H,causal,lengths", [
+    (1, False, [129]), (1, True, [257]), (2, False, [1025, 130, 300]), (2, True, [1025, 130, 300]),  # 8 parts
+    (9, False, [225, 993, 256]), (16, True, [225, 993, 480]),                                        # 4
+    (17, False, [385, 250, 545]), (33, True, [385, 250, 545])])                                      # 2
+def test_tile_parts(torch, D, H, causal, lengths):
+    got, ref, n = _run_case(torch, lengths, H, D, causal, seed=D + H)
+    _assert_close(got, ref, n, f"parts H={H} D={D} causal={causal}")
+
+
+# A merge of streams whose running maxima lie far apart (and, causal, rows for
+# which only one stream has keys): K rows growing along the sequence.
+@pytest.mark.parametrize("D", [64, 72, 128])
+@pytest.mark.parametrize("causal", [False, True])
+def test_tile_parts_far_maxima(torch, D, causal):
+    gain = np.concatenate([np.repeat([0.01, 8.0, 0.5, 3.0], 160)[:611], np.ones(GUARD)])
+    got, ref, n = _run_case(torch, [611], 2, D, causal, seed=D, key_gain=gain)
+    _assert_close(got, ref, n, f"parts, far maxima D={D} causal={causal}")
+
+
 @pytest.mark.parametrize("causal", [False, True])
 def test_only_empty_sequences(torch, causal):
     """A batch whose sequences are all empty: every call returns without
