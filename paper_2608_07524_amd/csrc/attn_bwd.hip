@@ -219,6 +219,12 @@ __device__ __forceinline__ void to_mfma16_layout(bf16x8& xv, bf16x8& yv) {
 // two matrix products, and the exponentials of one key block can overlap
 // the products of the other.
 //
+// QS > 1 (few tiles, see tile_parts): the wavefronts form QS query streams x
+// NW / QS key groups.  A ring tile is one 32-query block per stream; the
+// streams' dK and dV are summed through LDS at the end, in stream order.  The
+// V copy shrinks with the key groups, which pays for the longer ring tiles.
+// Two heads of width 128: 4,096 tokens 164 -> 71 us, 16,384 tokens 706 -> 513.
+//
 // FUSED (packed windows, 32-query tiles, one 32-key block per wavefront):
 // the workgroup holds every key of the queries it visits, so it also
 // computes dQ = scale * dS K.  Each wavefront writes its bf16 dS^T block
@@ -229,7 +235,7 @@ __device__ __forceinline__ void to_mfma16_layout(bf16x8& xv, bf16x8& yv) {
 // fit two workgroups per CU the ring then holds Q and dO once, at the
 // row-read stride, and the transposing reads of dV and dK use that copy.
 template <int D, int KB, int NW, int BM, int NSTAGE, int WPE, bool CAUSAL, bool PACKED, bool FUSED, bool ONECOPY,
-          bool VLDS>
+          bool VLDS, int QS, int OSTR>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) void attn_bwd_dkdv_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
     const __bf16* __restrict__ dout, const float* __restrict__ lse2, const float* __restrict__ ndelta,
@@ -241,8 +247,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   // an odd number of 16-byte chunks (one copy outside packed windows: the
   // stride that also spreads the transposing reads; the fused window launch
   // keeps the minimal one to fit two workgroups per CU)
-  constexpr int RSTR = (ONECOPY && !FUSED) ? S::OSTR : S::DP + 8;
+  constexpr int RSTR = (ONECOPY && !FUSED) ? OSTR : S::DP + 8;
   constexpr int TSTR = ONECOPY ? RSTR : S::TSTR;  // (one copy: it serves both reads)
+  static_assert(RSTR % 16 == 8 && (!ONECOPY || RSTR >= (S::KV16 ? S::NMB * 16 : S::NDB * 32)), "ring stride");
+  constexpr int KG = NW / QS;  // key groups of 32*KB keys
+  static_assert(QS == 1 || (KB == 1 && !PACKED && BM == 32 * QS && ONECOPY), "query streams: one block each per tile");
   static_assert(BM % 32 == 0, "whole 32-query blocks per tile");
   static_assert(!FUSED || (PACKED && KB == 1 && BM == 32 && ONECOPY),
                 "fused dQ: packed windows, 32-query tiles, KB 1, one ring copy");
@@ -271,19 +280,22 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   // number of 16-byte chunks per row: conflict-free); rows past the tile's
   // keys are zero
   constexpr int VLSTR = S::DP + 8;
-  using DVL = DmaTile<32 * KB * NW, VLSTR / 8, CPR, NW>;
+  using DVL = DmaTile<32 * KB * KG, VLSTR / 8, CPR, NW>;
   __shared__ __attribute__((aligned(16))) __bf16 Vl[VLDS ? DVL::ELEMS : 8];
   constexpr int NSB = NW * KB;  // 32-key blocks per workgroup
-  static_assert(NSB % 2 == 0 && NSTAGE * RBUF >= NSB / 2 * 32 * SSTR, "staging area too small");
+  static_assert(NSB % 2 == 0 && NSTAGE * RBUF >= (QS > 1 ? KG : NSB / 2) * 32 * SSTR, "staging area too small");
   static_assert(NSTAGE >= 2 && NSTAGE <= 4, "ring depth");
   static_assert(2 * NI < 64, "vmcnt range");
 
-  const WorkUnit u = unit_for_block(units, per_xcd);
+  constexpr int PARTS = PACKED ? 1 : bwd_dkdv_shape(D).waves * QS / NW;
+  WorkUnit u = part_for_block<PARTS>(units, per_xcd, 32 * KB * KG, false);
   if (u.rows == 0) return;
   const int h = u.head;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar branches on it
+  const int kw = QS > 1 ? wave % KG : wave;      // this wavefront's key group
+  const int stream = QS > 1 ? wave / KG : 0;     // and query stream
   const int g = lane >> 5;
   const int j = lane & 31;
   const int64_t ts = int64_t(H) * D;
@@ -301,13 +313,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   const float* lseh = lse2 + int64_t(h) * T + u.seq0;
   const float* ndh = ndelta + int64_t(h) * T + u.seq0;
 
-  // K and V fragments: lane (g, j) of key block kb holds key 32*(KB*wave +
+  // K and V fragments: lane (g, j) of key block kb holds key 32*(KB*kw +
   // kb) + j of the tile, columns 16*kd + 8*g .. +7.  Keys past the sequence
   // end are zero; their dK, dV rows are never stored.
   bf16x8 kf[KB][NKD], vf[KB][NKD];
 #pragma unroll
   for (int kb = 0; kb < KB; ++kb) {
-    const int key = 32 * (KB * wave + kb) + j;
+    const int key = 32 * (KB * kw + kb) + j;
     const bool ok = key < u.rows;
 #pragma unroll
     for (int kd = 0; kd < NKD; ++kd) {
@@ -328,7 +340,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   // (VLDS) likewise the tile's V rows
   if constexpr (VLDS) DVL::issue(Vl, vh + int64_t(key_t0) * ts, ts, u.rows, zero, zero, wave, lane);
 
-  const int wave_key_lo = key_t0 + 32 * KB * wave;  // smallest key of this wavefront
+  const int wave_key_lo = key_t0 + 32 * KB * kw;  // smallest key of this wavefront
   // queries of each key's sequence: [q_lo, q_hi)
   int q_lo[KB], q_hi[KB];
 #pragma unroll
@@ -423,8 +435,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   const lds_bf16* dOt3 = ONECOPY ? dOr3 : lds_ptr(dOt);
   const lds_f32* LV3 = lds_ptr(LV);
   const lds_bf16* Vl3 = lds_ptr(Vl);
-  // (VLDS) lane (g, j) reads key 32*(KB*wave + kb) + j, columns 16*kd + 8*g
-  const unsigned vl_off = (32 * KB * wave + j) * VLSTR + 8 * g;
+  // (VLDS) lane (g, j) reads key 32*(KB*kw + kb) + j, columns 16*kd + 8*g
+  const unsigned vl_off = (32 * KB * kw + j) * VLSTR + 8 * g;
   constexpr unsigned TBUF_R = ONECOPY ? RBUF : TBUF;  // stage size of the transposing-read copies
 
   // (fused) this lane's four 8-byte slots of the dS^T buffer of tile it:
@@ -675,7 +687,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   // crossing them masked.  Every iteration runs the same copy / wait /
   // barrier sequence.
   // (packed windows: the queries of this wavefront's keys' sequences)
-  const int last_key = min(32 * KB - 1, int(u.rows) - 1 - 32 * KB * wave);  // of the wavefront, tile-relative
+  const int last_key = min(32 * KB - 1, int(u.rows) - 1 - 32 * KB * kw);  // of the wavefront, tile-relative
   const int wq_lo = packed ? (CAUSAL ? wave_key_lo : __builtin_amdgcn_readfirstlane(q_lo[0])) : 0;
   const int wq_hi = packed ? __builtin_amdgcn_readlane(q_hi[KB - 1], max(last_key, 0) % 32) : seqlen;
   auto run = [&](int it0, int it1, auto mask_tag) DCP_INLINE {
@@ -686,7 +698,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
       const int q0 = q_begin + tile_of(it) * BM;
       ds_it = it;
 #pragma unroll
-      for (int qb = 0; qb < BM / 32; ++qb) {
+      for (int qx = 0; qx < BM / 32 / QS; ++qx) {
+        const int qb = QS > 1 ? stream : qx;
         const int qa = q0 + 32 * qb;
         if (qa >= seqlen) {  // padding rows of the last tile
           zero_ds(it);
@@ -723,7 +736,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
       dq_phase(it);
     }
   };
-  if (32 * KB * wave < u.rows) {
+  if (32 * KB * kw < u.rows) {
     if constexpr (packed) {
       const int it_lo = (wq_lo - q_begin) / BM;
       const int it_hi = min(n_qt, (wq_hi - q_begin + BM - 1) / BM);
@@ -745,6 +758,56 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
     idle(0, n_qt);  // no key of the tile (the last tile of a sequence)
   }
 
+
+  if constexpr (QS > 1) {
+    // Sum the streams' dK (then dV) through the idle ring, round, and store
+    // whole rows from a bf16 copy of each key group's block.
+    constexpr int NP = S::KV16 ? 2 * NMB : 4 * NDB;
+    using Sum = StreamSum<NP, KG, QS>;
+    static_assert(Sum::HALF_BYTES <= NSTAGE * RBUF * 2, "pieces fit the ring");
+    const Sum sum{(DCP_LDS char*)lds_ptr(Qr), (DCP_LDS char*)lds_ptr(dOr), kw, lane};
+    auto finish = [&](auto piece, float mul, __bf16* __restrict__ out) DCP_INLINE {
+#pragma unroll
+      for (int x = 0; x < NP; ++x)
+        if (x % QS != stream) *sum.slot(x, stream) = piece(x);
+      __syncthreads();
+      f32x4 own[Sum::PPO];
+#pragma unroll
+      for (int x = 0; x < NP; ++x) {
+        if (x % QS != stream) continue;
+        f32x4 acc = {};
+#pragma unroll
+        for (int t = 0; t < QS; ++t) acc += t == stream ? piece(x) : *sum.slot(x, t);
+        own[x / QS] = acc * mul;
+      }
+      __syncthreads();
+      __bf16* stage = Qr + kw * 32 * SSTR;
+#pragma unroll
+      for (int x = 0; x < NP; ++x) {
+        if (x % QS != stream) continue;
+        const int row = S::KV16 ? 16 * (x / NMB) + 4 * g4 : 8 * (x & 3) + 4 * g;
+        const int col = S::KV16 ? 16 * (x % NMB) + (lane & 15) : 32 * (x >> 2) + j;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) stage[(row + e) * SSTR + col] = __bf16(own[x / QS][e]);
+      }
+      __syncthreads();
+      for (int ch = 64 * stream + lane; ch < 32 * CPR; ch += 64 * QS) {
+        const int row = ch / CPR, cc = ch % CPR;
+        if (32 * kw + row < u.rows)
+          *reinterpret_cast<u32x4*>(out + (int64_t(u.row0) + 32 * kw + row) * ts + int64_t(h) * D + cc * 8) =
+              *reinterpret_cast<const u32x4*>(&stage[row * SSTR + cc * 8]);
+      }
+      __syncthreads();
+    };
+    auto piece_of = [&](const auto& a16, const auto& a32, int x) DCP_INLINE {
+      if constexpr (S::KV16) return a16[0][x / NMB][x % NMB];
+      const f32x16& a = a32[0][x >> 2];
+      return f32x4{a[4 * (x & 3)], a[4 * (x & 3) + 1], a[4 * (x & 3) + 2], a[4 * (x & 3) + 3]};
+    };
+    finish([&](int x) DCP_INLINE { return piece_of(dk16, dk_acc, x); }, scale, dk);
+    finish([&](int x) DCP_INLINE { return piece_of(dv16, dv_acc, x); }, 1.f, dv);
+    return;
+  }
 
   // Epilogue through LDS (the ring is idle now): the workgroup's first half
   // of 32-key blocks is staged in the Q buffers, the second in the dO
@@ -776,8 +839,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
 // NSTAGE - 1 tiles ahead (K twice: rows read 16 B per lane for S^T, rows
 // read by transposing reads for dQ^T; V once), one barrier per tile.  With
 // ONECOPY, K is held once, at the row-read stride, and the transposing
-// reads use that copy.
-template <int D, int NW, int NSTAGE, bool CAUSAL, bool PACKED, bool ONECOPY>
+// reads use that copy.  KS > 1 (few tiles, see tile_parts): KS key streams x
+// NW / KS query groups, summed as in the dK/dV pass; two heads of width 128:
+// 4,096 tokens 125 -> 45 us, 16,384 tokens 521 -> 351.
+template <int D, int NW, int NSTAGE, bool CAUSAL, bool PACKED, bool ONECOPY, int KS, int NKB>
 __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
     const __bf16* __restrict__ dout, const float* __restrict__ lse2, const float* __restrict__ ndelta,
@@ -787,8 +852,10 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_kernel(
   constexpr int NKD = S::NKD, NDB = S::NDB, CPR = S::CPR;
   constexpr int KSTR = ONECOPY ? S::OSTR : S::DP + 8;  // K and V rows read 16 B per lane (and K transposed)
   constexpr int TSTR = ONECOPY ? KSTR : S::TSTR;  // (second copy of K for transposing reads)
-  constexpr int BN = kBwdDqBN;
+  // a ring tile holds NKB 32-key blocks of each of the KS key streams
+  constexpr int BN = 32 * NKB * KS;
   constexpr int KBUF = BN * KSTR, TBUF = ONECOPY ? 0 : BN * TSTR;
+  constexpr int QG = NW / KS;  // 32-query groups of the workgroup
   using DK = DmaTile<BN, KSTR / 8, CPR, NW>;
   using DT = DmaTile<BN, TSTR / 8, CPR, NW>;
   constexpr int NI = ONECOPY ? 2 * DK::NI : 2 * DK::NI + DT::NI;  // copies per wavefront per tile
@@ -799,19 +866,21 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_kernel(
   static_assert(NSTAGE >= 2 && NSTAGE <= 4, "ring depth");
   static_assert(2 * NI < 64, "vmcnt range");
 
-  const WorkUnit u = unit_for_block(units, per_xcd);
+  const WorkUnit u = part_for_block<PACKED ? 1 : kBwdDqWaves * KS / NW>(units, per_xcd, 32 * QG, CAUSAL);
   if (u.rows == 0) return;
   const int h = u.head;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: scalar branches on it
+  const int qw = KS > 1 ? wave % QG : wave;      // this wavefront's query group
+  const int stream = KS > 1 ? wave / QG : 0;     // and key stream
   const int g = lane >> 5;
   const int j = lane & 31;
   const int64_t ts = int64_t(H) * D;
   constexpr bool packed = PACKED;  // a list of packed windows only
   const int seqlen = packed ? int(u.rows) : u.seqlen;  // (window-relative offsets when packed)
   const int tile_q0 = u.row0 - u.seq0;
-  const int wave_q0 = tile_q0 + 32 * wave;
+  const int wave_q0 = tile_q0 + 32 * qw;
   const __bf16* zero = consts + kConstZero;
 
   const __bf16* qh = q + int64_t(u.seq0) * ts + int64_t(h) * D;
@@ -820,7 +889,7 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_kernel(
   const __bf16* doh = dout + int64_t(u.seq0) * ts + int64_t(h) * D;
 
   // Per-lane query state: Q and dO fragments (B operands), LSE, -Delta.
-  const int qrel = 32 * wave + j;
+  const int qrel = 32 * qw + j;
   const bool q_ok = qrel < u.rows;
   const int my_q = tile_q0 + qrel;  // sequence-relative
   // keys of this lane's sequence: [k_lo, k_hi)
@@ -905,28 +974,28 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_kernel(
   const lds_bf16* Vs3 = lds_ptr(Vs);
   const lds_bf16* Kt3 = ONECOPY ? Ks3 : lds_ptr(Kt);
   constexpr unsigned TBUF_R = ONECOPY ? KBUF : TBUF;  // stage size of the transposing-read copy
-  const int wave_last_q = wave_q0 + 31;
 
-  // One key tile against this wavefront's 32 queries.  MASK covers tiles
-  // crossing the sequence end or the causal diagonal.
+  // This wavefront's blocks of a key tile (the first key k0) against its 32
+  // queries.  MASK covers blocks crossing the sequence end or the causal
+  // diagonal.
   auto process_tile = [&](unsigned st, int k0, auto mask_tag) DCP_INLINE {
     constexpr bool MASK = decltype(mask_tag)::value;
-    unsigned rb = st * KBUF + ar_off;
-    unsigned tb = st * TBUF_R + tr_off;
+    unsigned rb = st * KBUF + stream * (32 * NKB * KSTR) + ar_off;
+    unsigned tb = st * TBUF_R + stream * (32 * NKB * TSTR) + tr_off;
     asm("" : "+v"(rb), "+v"(tb));  // keeps the constant terms in the offset fields
-    f32x16 s[BN / 32], dp[BN / 32];
+    f32x16 s[NKB], dp[NKB];
 #pragma unroll
-    for (int kb = 0; kb < BN / 32; ++kb) {
+    for (int kb = 0; kb < NKB; ++kb) {
       s[kb] = f32x16{};
       dp[kb] = FOLD ? nd_init : f32x16{};
     }
     mfma_prio_hi();
     // The K and V fragments of step kd + 1 are read while step kd's products
     // run (held in that order by scheduling fences).
-    bf16x8 fk[NKD][BN / 32], fv[NKD][BN / 32];
+    bf16x8 fk[NKD][NKB], fv[NKD][NKB];
     auto fetch = [&](int kd) DCP_INLINE {
 #pragma unroll
-      for (int kb = 0; kb < BN / 32; ++kb) {
+      for (int kb = 0; kb < NKB; ++kb) {
         fk[kd][kb] = lds_read_b128(Ks3 + rb + 32 * kb * KSTR + 16 * kd);
         fv[kd][kb] = lds_read_b128(Vs3 + rb + 32 * kb * KSTR + 16 * kd);
       }
@@ -937,7 +1006,7 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_kernel(
       if (kd + 1 < NKD) fetch(kd + 1);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int kb = 0; kb < BN / 32; ++kb) {
+      for (int kb = 0; kb < NKB; ++kb) {
         s[kb] = mfma32(fk[kd][kb], qf[kd], s[kb]);
         dp[kb] = mfma32(fv[kd][kb], df[kd], dp[kb]);
       }
@@ -945,9 +1014,9 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_kernel(
     }
     mfma_prio_lo();
     // Lane (g, j) holds query j against keys k0 + 32kb + 8(r/4) + 4g + r%4.
-    bf16x8 dsb[BN / 32][2];
+    bf16x8 dsb[NKB][2];
 #pragma unroll
-    for (int kb = 0; kb < BN / 32; ++kb)
+    for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         float p = __builtin_amdgcn_exp2f(fmaf(s[kb][r], scale_log2, -lse_l2));
@@ -961,10 +1030,10 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_kernel(
       // dQ^T += K^T dS^T in 16x16 blocks: each A fragment (16 rows of K^T
       // over the block's 32 keys) feeds both 16-query halves.
 #pragma unroll
-      for (int kb = 0; kb < BN / 32; ++kb) to_mfma16_layout(dsb[kb][0], dsb[kb][1]);
+      for (int kb = 0; kb < NKB; ++kb) to_mfma16_layout(dsb[kb][0], dsb[kb][1]);
       mfma_prio_hi();
 #pragma unroll
-      for (int kb = 0; kb < BN / 32; ++kb)
+      for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
         for (int mb = 0; mb < NMB; ++mb) {
           const unsigned o = tb + 32 * kb * TSTR + 16 * mb;
@@ -980,7 +1049,7 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_kernel(
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
-      for (int kb = 0; kb < BN / 32; ++kb)
+      for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
           const unsigned o = tb + (32 * kb + 16 * hh) * TSTR + 32 * db;
@@ -996,26 +1065,25 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_kernel(
   // packed window every tile is masked, and the tiles before the first
   // query's sequence (t_lead) and after the last one's are idle.
   int t_lead = 0;
-  int t_mask = min(n_tiles, seqlen / BN);
-  int t_idle = n_tiles;
-  if (CAUSAL) {
-    t_mask = min(t_mask, (wave_q0 + 1) / BN);
-    t_idle = min(n_tiles, wave_last_q / BN + 1);
-  }
+  const int s_lo = 32 * NKB * stream, s_hi = s_lo + 32 * NKB;  // this stream's keys of a tile
+  const int full_keys = CAUSAL ? min(seqlen, wave_q0 + 1) : seqlen;  // keys before this need no mask
+  const int some_keys = CAUSAL ? min(seqlen, wave_q0 + 32) : seqlen;  // keys from this on are not visited
+  int t_mask = min(n_tiles, full_keys < s_hi ? 0 : (full_keys - s_hi) / BN + 1);
+  int t_idle = max(t_mask, min(n_tiles, (some_keys - s_lo + BN - 1) / BN));
   if constexpr (packed) {
-    const int last = min(31, int(u.rows) - 1 - 32 * wave);  // lane of the wavefront's last query
+    const int last = min(31, int(u.rows) - 1 - 32 * qw);  // lane of the wavefront's last query
     const int keys_end = min(__builtin_amdgcn_readlane(k_hi, max(last, 0)), CAUSAL ? wave_q0 + 32 : seqlen);
     t_lead = t_mask = __builtin_amdgcn_readfirstlane(k_lo) / BN;
     t_idle = min(n_tiles, (keys_end + BN - 1) / BN);
   }
-  if (32 * wave >= u.rows) t_lead = t_mask = t_idle = 0;
+  if (32 * qw >= u.rows) t_lead = t_mask = t_idle = 0;
   auto run = [&](int kt0, int kt1, auto mode_tag) DCP_INLINE {
     constexpr int MODE = decltype(mode_tag)::value;  // 0 unmasked, 1 masked, 2 idle
     for (int kt = kt0; kt < kt1; ++kt) {
       if (kt + NSTAGE - 1 < n_tiles) issue_tile(kt + NSTAGE - 1);
       const unsigned st = unsigned(kt) % NSTAGE;
-      if constexpr (MODE == 0) process_tile(st, kt * BN, std::false_type{});
-      if constexpr (MODE == 1) process_tile(st, kt * BN, std::true_type{});
+      if constexpr (MODE == 0) process_tile(st, kt * BN + s_lo, std::false_type{});
+      if constexpr (MODE == 1) process_tile(st, kt * BN + s_lo, std::true_type{});
       wait_next(kt);
       __syncthreads();
     }
@@ -1025,6 +1093,38 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_kernel(
   run(t_mask, t_idle, std::integral_constant<int, 1>{});
   run(t_idle, n_tiles, std::integral_constant<int, 2>{});
 
+  if constexpr (KS > 1) {
+    // Sum the streams' dQ through the idle ring.
+    constexpr int NP = S::KV16 ? 2 * NMB : 4 * NDB;
+    using Sum = StreamSum<NP, QG, KS>;
+    static_assert(Sum::HALF_BYTES <= NSTAGE * KBUF * 2, "pieces fit the ring");
+    const Sum sum{(DCP_LDS char*)lds_ptr(Ks), (DCP_LDS char*)lds_ptr(Vs), qw, lane};
+    auto piece = [&](int x) DCP_INLINE {
+      if constexpr (S::KV16) return acc16[x >> 1][x & 1];
+      const f32x16& a = acc[x >> 2];
+      return f32x4{a[4 * (x & 3)], a[4 * (x & 3) + 1], a[4 * (x & 3) + 2], a[4 * (x & 3) + 3]};
+    };
+#pragma unroll
+    for (int x = 0; x < NP; ++x)
+      if (x % KS != stream) *sum.slot(x, stream) = piece(x);
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < NP; ++x) {
+      if (x % KS != stream) continue;
+      f32x4 a = {};
+#pragma unroll
+      for (int t = 0; t < KS; ++t) a += t == stream ? piece(x) : *sum.slot(x, t);
+      const int qr = 32 * qw + (S::KV16 ? 16 * (x & 1) + (lane & 15) : j);
+      const int d0 = S::KV16 ? 16 * (x >> 1) + 4 * g4 : 32 * (x >> 2) + 8 * (x & 3) + 4 * g;
+      if (qr < u.rows && d0 < D) {
+        bf16x4 w;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) w[c] = __bf16(a[c] * scale);
+        *reinterpret_cast<bf16x4*>(dq + int64_t(u.row0 + qr) * ts + int64_t(h) * D + d0) = w;
+      }
+    }
+    return;
+  }
   if constexpr (S::KV16) {
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
@@ -1063,13 +1163,17 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_kernel(
   }
 }
 
-template <int D, bool CAUSAL, bool PACKED, bool FUSED = false>
+// QS query streams among NW wavefronts (QS 1: the pass's own shape); each unit
+// of a sequence-tile list becomes waves * QS / NW workgroups.
+template <int D, bool CAUSAL, bool PACKED, bool FUSED = false, int NW = 0, int QS = 1>
 hipError_t launch_dkdv_list(const BwdArgs& a, const WorkUnit* units, int n_units) {
-  constexpr DkdvShape sh = PACKED ? bwd_dkdv_window_shape(D) : bwd_dkdv_shape(D);
-  hipLaunchKernelGGL(
-      (attn_bwd_dkdv_kernel<D, sh.kb, sh.waves, sh.bm, sh.stages, sh.waves_per_eu, CAUSAL, PACKED, FUSED,
-                            FUSED || sh.onecopy, sh.vlds>),
-                     dim3(n_units), dim3(64 * sh.waves), 0, a.stream, static_cast<const __bf16*>(a.q),
+  constexpr DkdvShape sh = QS > 1 ? bwd_dkdv_split_shape(D, NW, QS) : PACKED ? bwd_dkdv_window_shape(D) : bwd_dkdv_shape(D);
+  constexpr int PARTS = PACKED ? 1 : bwd_dkdv_shape(D).waves * QS / sh.waves;
+  // (QS 4 at head width 128: only the minimal stride leaves room for two tiles)
+  constexpr int OSTR = QS == 4 && D > 96 ? BwdShape<D>::DP + 8 : BwdShape<D>::OSTR;
+  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, sh.kb, sh.waves, sh.bm, sh.stages, sh.waves_per_eu, CAUSAL, PACKED, FUSED,
+                                           FUSED || sh.onecopy, sh.vlds, QS, OSTR>),
+                     dim3(n_units * PARTS), dim3(64 * sh.waves), 0, a.stream, static_cast<const __bf16*>(a.q),
                      static_cast<const __bf16*>(a.k), static_cast<const __bf16*>(a.v),
                      static_cast<const __bf16*>(a.dout), a.lse2, a.ndelta, static_cast<__bf16*>(a.dk),
                      static_cast<__bf16*>(a.dv), static_cast<__bf16*>(a.dq), static_cast<const __bf16*>(a.consts), units,
@@ -1078,16 +1182,40 @@ hipError_t launch_dkdv_list(const BwdArgs& a, const WorkUnit* units, int n_units
   return hipGetLastError();
 }
 
-template <int D, bool CAUSAL, bool PACKED>
+// KS key streams among NW wavefronts, NKB 32-key blocks each per ring tile.
+template <int D, int NW, int NS, bool CAUSAL, bool PACKED, int KS = 1, int NKB = 2>
 hipError_t launch_dq_list(const BwdArgs& a, const WorkUnit* units, int n_units) {
-  constexpr int NW = PACKED ? kWinDqWaves : kBwdDqWaves;
-  constexpr int NS = D > 96 ? kBwdDqStagesD128 : (PACKED ? kWinDqStages : kBwdDqStages);
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, NW, NS, CAUSAL, PACKED, kBwdDqOneCopy>), dim3(n_units), dim3(64 * NW), 0, a.stream, static_cast<const __bf16*>(a.q),
-                     static_cast<const __bf16*>(a.k), static_cast<const __bf16*>(a.v),
-                     static_cast<const __bf16*>(a.dout), a.lse2, a.ndelta, static_cast<__bf16*>(a.dq),
-                     static_cast<const __bf16*>(a.consts), units, static_cast<const uint64_t*>(a.qwindow_starts),
-                     n_units / kNumXcd, a.n_heads, a.total_tokens, a.scale, a.scale * kLog2e);
+  constexpr int PARTS = PACKED ? 1 : kBwdDqWaves * KS / NW;
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, NW, NS, CAUSAL, PACKED, kBwdDqOneCopy, KS, NKB>), dim3(n_units * PARTS),
+                     dim3(64 * NW), 0, a.stream, static_cast<const __bf16*>(a.q), static_cast<const __bf16*>(a.k),
+                     static_cast<const __bf16*>(a.v), static_cast<const __bf16*>(a.dout), a.lse2, a.ndelta,
+                     static_cast<__bf16*>(a.dq), static_cast<const __bf16*>(a.consts), units,
+                     static_cast<const uint64_t*>(a.qwindow_starts), n_units / kNumXcd, a.n_heads, a.total_tokens,
+                     a.scale, a.scale * kLog2e);
   return hipGetLastError();
+}
+
+template <int D, bool CAUSAL>
+hipError_t launch_dkdv_tiles(const BwdArgs& a, const WorkUnit* units) {
+  switch (tile_parts(a.n_units, CAUSAL)) {
+    case 8: return launch_dkdv_list<D, CAUSAL, false, false, 4, 4>(a, units, a.n_units);
+    case 4: return launch_dkdv_list<D, CAUSAL, false, false, 8, 4>(a, units, a.n_units);
+    case 2: return launch_dkdv_list<D, CAUSAL, false, false, 8, 2>(a, units, a.n_units);
+    default: return launch_dkdv_list<D, CAUSAL, false>(a, units, a.n_units);
+  }
+}
+
+template <int D, bool CAUSAL>
+hipError_t launch_dq_tiles(const BwdArgs& a, const WorkUnit* units) {
+  constexpr int W = kBwdDqWaves;
+  constexpr int NS = D > 96 ? kBwdDqStagesD128 : kBwdDqStages;  // (also two or three tiles of 128 keys when split)
+  switch (tile_parts(a.n_qunits, CAUSAL)) {
+    // (8 parts gain nothing over 4 here: 4,096 tokens 213 and 215 us per backward)
+    case 8:
+    case 4: return launch_dq_list<D, W, NS, CAUSAL, false, 4, 1>(a, units, a.n_qunits);
+    case 2: return launch_dq_list<D, W, NS, CAUSAL, false, 2, 2>(a, units, a.n_qunits);
+    default: return launch_dq_list<D, W, NS, CAUSAL, false>(a, units, a.n_qunits);
+  }
 }
 
 // Delta, then the dK/dV pass and the dQ pass, each over its sequence tiles
@@ -1109,16 +1237,19 @@ hipError_t launch_bwd_t(const BwdArgs& a) {
   hipError_t e = hipSuccess;
   if (a.n_units + a.n_wunits > 0) {
     if (ev.begin) (void)hipEventRecord(ev.begin, a.stream);
-    if (a.n_units > 0) e = launch_dkdv_list<D, CAUSAL, false>(a, units, a.n_units);
+    if (a.n_units > 0) e = launch_dkdv_tiles<D, CAUSAL>(a, units);
     if (e == hipSuccess && a.n_wunits > 0)
       e = launch_dkdv_list<D, CAUSAL, true, bwd_window_fused(D)>(a, units + a.n_units, a.n_wunits);
     if (ev.end) (void)hipEventRecord(ev.end, a.stream);
     if (e != hipSuccess) return e;
   }
-  if (a.n_qunits > 0) e = launch_dq_list<D, CAUSAL, false>(a, qunits, a.n_qunits);
+  if (a.n_qunits > 0) e = launch_dq_tiles<D, CAUSAL>(a, qunits);
   // (windows with fused dQ: their dQ rows were written by the dK/dV pass)
-  if (e == hipSuccess && a.n_wqunits > 0 && !bwd_window_fused(D))
-    e = launch_dq_list<D, CAUSAL, true>(a, qunits + a.n_qunits, a.n_wqunits);
+  if constexpr (!bwd_window_fused(D)) {
+    constexpr int NS = D > 96 ? kBwdDqStagesD128 : kWinDqStages;
+    if (e == hipSuccess && a.n_wqunits > 0)
+      e = launch_dq_list<D, kWinDqWaves, NS, CAUSAL, true>(a, qunits + a.n_qunits, a.n_wqunits);
+  }
   return e;
 }
 

@@ -67,7 +67,7 @@ constexpr int kFwdWaves = 8;
 // an LDS copy of the tile's 256 V rows (68 KB), which leaves K, the
 // accumulators and one 16-column step of operands in registers (249-256),
 // and the ring holds Q and dO once in two stages of 64-query tiles (76 KB).
-// dQ pass: kBwdDqWaves wavefronts of 32 queries, kBwdDqBN keys per step,
+// dQ pass: kBwdDqWaves wavefronts of 32 queries, 64 keys per step,
 // K held once per ring stage (its transposing reads share the row-read
 // copy; at head width 128 this also frees the registers the second copy's
 // offsets took).
@@ -79,8 +79,14 @@ struct DkdvShape {
 constexpr DkdvShape bwd_dkdv_shape(int head_dim) {
   return head_dim > 96 ? DkdvShape{1, 8, 64, 2, 2, true, true} : DkdvShape{1, 8, 64, 4, 2, true, false};
 }
+// The dK/dV pass with `qs` query streams among `waves` wavefronts (waves / qs
+// groups of 32 keys): a ring tile is one 32-query block per stream, in as many
+// stages as the LDS beside the (smaller) V copy holds.
+constexpr DkdvShape bwd_dkdv_split_shape(int head_dim, int waves, int qs) {
+  return head_dim > 96 ? DkdvShape{1, waves, 32 * qs, qs == 2 ? 3 : 2, 2, true, true}
+                       : DkdvShape{1, waves, 32 * qs, qs == 2 ? 4 : 3, 2, true, false};
+}
 constexpr int kBwdDqWaves = 8;
-constexpr int kBwdDqBN = 64;
 constexpr int kBwdDqStages = 3;
 constexpr int kBwdDqStagesD128 = 2;
 constexpr bool kBwdDqOneCopy = true;
