@@ -397,8 +397,9 @@ int dcp_plan(const int64_t* seq_lens, int32_t n_seqs, const int32_t* batch_offse
  *   out = h + a Wdown.
  * RMSNorm(z; g) = z * g / sqrt(mean(z^2) + eps) per row.  hidden = H*D of
  * `attn`, at most 4096 (DCP_ERR_UNSUPPORTED beyond); every row of x is a
- * token of some sequence (cu_seqlens[n] must equal total_tokens).  GEMMs run in rocBLAS (bf16 in, fp32 accumulation)
- * with their scratch taken from the caller's workspace; the rocBLAS handle
+ * token of some sequence (cu_seqlens[n] must equal total_tokens).  Weight gradients
+ * are formed by one HIP kernel, the other GEMMs run in rocBLAS (bf16 in, fp32
+ * accumulation), with their scratch taken from the caller's workspace; the rocBLAS handle
  * (one per thread and device, kept until the thread ends) is the only
  * device memory the library itself holds.
  */

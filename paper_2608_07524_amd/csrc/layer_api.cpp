@@ -8,7 +8,8 @@
 //   o  = attention(q, k, v) per sequence (the HIP kernels of this library),
 //   h  = x + o Wo,  y2 = RMSNorm(h; g2),  u = y2 Wup ([T, 4 hidden]),
 //   a  = GELU(u),   out = h + a Wdown.
-// GEMMs are plain library GEMMs (rocBLAS, bf16 inputs, fp32 compute); the
+// The activations' GEMMs are plain library GEMMs (rocBLAS, bf16 inputs, fp32
+// compute); the weight gradients are formed together by layer_gemm.hip, the
 // norms and the activation are the kernels of layer.hip.  A forward with a
 // stash keeps every activation the backward needs; with no stash it keeps
 // nothing and the backward runs the forward again first (recomputation).
@@ -290,32 +291,37 @@ extern "C" int dcp_layer_bwd(const dcp_layer_desc* L, const dcp_layer_weights* w
   }
   const int64_t T = d.T, h = d.h;
   float* partial = reinterpret_cast<float*>(at(workspace, b.partial));
-  // MLP: dA = dout Wdown^T; dWdown += A^T dout; dU = dA * GELU'(U) (in place)
+  // MLP: dA = dout Wdown^T; dU = dA * GELU'(U) (in place)
   DCP_TRY(gemm(hd, false, true, T, 4 * h, h, dout, w->w_down, 0.f, at(workspace, b.da), at(workspace, b.da), false));
-  DCP_TRY(gemm(hd, true, false, 4 * h, h, T, at(sb, s.a), dout, 1.f, g->w_down, g->w_down, true));
   DCP_HIP(launch_gelu_bwd(at(sb, s.u), at(workspace, b.da), at(workspace, b.da), T * 4 * h, st));
-  // dY2 = dU Wup^T (fp32); dWup += Y2^T dU; dH = dout + RMSNorm backward
+  // dY2 = dU Wup^T (fp32); dH = dout + RMSNorm backward
   DCP_TRY(gemm(hd, false, true, T, h, 4 * h, at(workspace, b.da), w->w_up, 0.f, at(workspace, b.dy2),
                at(workspace, b.dy2), true));
-  DCP_TRY(gemm(hd, true, false, h, 4 * h, T, at(sb, s.y2), at(workspace, b.da), 1.f, g->w_up, g->w_up, true));
   DCP_HIP(launch_rmsnorm_bwd(reinterpret_cast<float*>(at(workspace, b.dy2)), at(sb, s.hres), w->norm2,
                              reinterpret_cast<float*>(at(sb, s.rstd2)), dout, at(workspace, b.dh), partial, g->norm2, T,
                              int(h), st));
-  // attention block: dO = dH Wo^T; dWo += O^T dH; attention backward
+  // attention block: dO = dH Wo^T; attention backward
   void* dO = at(workspace, b.dy1);  // dY1 is not needed yet: its space holds dO (bf16) first
   DCP_TRY(gemm(hd, false, true, T, h, h, at(workspace, b.dh), w->wo, 0.f, dO, dO, false));
-  DCP_TRY(gemm(hd, true, false, h, h, T, at(sb, s.o), at(workspace, b.dh), 1.f, g->wo, g->wo, true));
   DCP_TRY(dcp_varlen_attn_bwd(L->attn, dO, at(sb, s.o), reinterpret_cast<const float*>(at(sb, s.lse)), at(sb, s.q),
                               at(sb, s.k), at(sb, s.v), at(workspace, b.dq), at(workspace, b.dk), at(workspace, b.dv),
                               at(workspace, b.attn_b), b.stash - b.attn_b, st));
-  // dY1 = dQ Wq^T + dK Wk^T + dV Wv^T (fp32); dW{q,k,v} += Y1^T d{Q,K,V}
+  // dY1 = dQ Wq^T + dK Wk^T + dV Wv^T (fp32)
   void* dY1 = at(workspace, b.dy1);
   DCP_TRY(gemm(hd, false, true, T, h, h, at(workspace, b.dq), w->wq, 0.f, dY1, dY1, true));
   DCP_TRY(gemm(hd, false, true, T, h, h, at(workspace, b.dk), w->wk, 1.f, dY1, dY1, true));
   DCP_TRY(gemm(hd, false, true, T, h, h, at(workspace, b.dv), w->wv, 1.f, dY1, dY1, true));
-  DCP_TRY(gemm(hd, true, false, h, h, T, at(sb, s.y1), at(workspace, b.dq), 1.f, g->wq, g->wq, true));
-  DCP_TRY(gemm(hd, true, false, h, h, T, at(sb, s.y1), at(workspace, b.dk), 1.f, g->wk, g->wk, true));
-  DCP_TRY(gemm(hd, true, false, h, h, T, at(sb, s.y1), at(workspace, b.dv), 1.f, g->wv, g->wv, true));
+  // every weight gradient in one launch: dWdown += A^T dout, dWup += Y2^T dU,
+  // dWo += O^T dH, dW{q,k,v} += Y1^T d{Q,K,V}
+  const int hi = int(h);
+  const WgradBatch wb{{{at(sb, s.a), dout, g->w_down, 4 * hi, hi, 0},
+                       {at(sb, s.y2), at(workspace, b.da), g->w_up, hi, 4 * hi, 0},
+                       {at(sb, s.o), at(workspace, b.dh), g->wo, hi, hi, 0},
+                       {at(sb, s.y1), at(workspace, b.dq), g->wq, hi, hi, 0},
+                       {at(sb, s.y1), at(workspace, b.dk), g->wk, hi, hi, 0},
+                       {at(sb, s.y1), at(workspace, b.dv), g->wv, hi, hi, 0}},
+                      T, 0, 0};
+  DCP_HIP(launch_wgrad(wb, at(workspace, b.gemm), kGemmWorkspace, st));
   // dX = dH + RMSNorm backward of dY1
   DCP_HIP(launch_rmsnorm_bwd(reinterpret_cast<float*>(dY1), x, w->norm1, reinterpret_cast<float*>(at(sb, s.rstd1)),
                              at(workspace, b.dh), dx, partial, g->norm1, T, int(h), st));

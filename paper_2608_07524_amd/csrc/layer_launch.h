@@ -1,4 +1,4 @@
-// Host-side launch interface of the layer kernels (layer.hip).
+// Host-side launch interface of the layer kernels (layer.hip, layer_gemm.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -15,6 +15,24 @@ hipError_t launch_rmsnorm_bwd(const float* dy, const void* x, const void* g, con
                               void* dx, float* partial, float* dg, int64_t rows, int h, hipStream_t s);
 int64_t rmsnorm_bwd_blocks(int64_t rows);
 // a = GELU(u) and du = da * GELU'(u), n elements (a multiple of 8), bf16.
+// Weight gradients c[m, n] (fp32) += a^T b over the batch's tokens, a [tokens,
+// m] and b [tokens, n] bf16 row-major (m, n multiples of 8); scratch holds
+// partial sums (256-byte aligned).
+constexpr int kWgradMax = 6;  // a layer's weight matrices
+struct WgradProblem {
+  const void* a;
+  const void* b;
+  float* c;
+  int m, n;
+  int tile0;  // (set by the launch)
+};
+struct WgradBatch {
+  WgradProblem p[kWgradMax];
+  int64_t tokens;
+  int n_tiles, splits;  // (set by the launch)
+};
+hipError_t launch_wgrad(WgradBatch b, void* scratch, size_t scratch_bytes, hipStream_t s);
+
 hipError_t launch_gelu_fwd(const void* u, void* a, int64_t n, hipStream_t s);
 hipError_t launch_gelu_bwd(const void* u, const void* da, void* du, int64_t n, hipStream_t s);
 

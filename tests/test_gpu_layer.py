@@ -86,6 +86,29 @@ def test_layer_matches_oracle(torch, causal):
     assert max(errs.values()) <= GRAD_TOL, errs
 
 
+# The weight gradients' output tiles are 192 x 192 and their token slices 32
+# rows; with fewer than 256 tiles the tokens are split as well, in at least
+# eight slices each.  Widths below, at and across the tile; one token, a slice
+# and its neighbours, an uneven split; and a width with tiles enough for no
+# split.  Gradients add to what is there.
+@pytest.mark.parametrize("H,D,lengths", [(1, 64, [1]), (3, 64, [31, 2]), (3, 72, [32]), (5, 64, [900, 133]),
+                                         (2, 128, [1025]), (16, 72, [33, 32])])
+def test_weight_gradients(torch, H, D, lengths):
+    layer, cu, Wb, xb, db, x, dout = _setup(torch, lengths, H, D, True, 31 + H)
+    for g in layer.grads.values():
+        g.fill_(3.0)
+    layer.fwd(x)
+    layer.bwd(x, dout)
+    torch.cuda.synchronize()
+    _, cache = LY.layer_forward(xb, Wb, cu, H, D, 1.0 / math.sqrt(D), True, 1e-6)
+    _, ref = LY.layer_backward(db, Wb, cache, cu, H, D, 1.0 / math.sqrt(D), True)
+    errs = {n: float(np.max(np.abs(layer.grads[n].cpu().numpy().astype(np.float64) - 3.0 - ref[n]))
+                     / np.max(np.abs(ref[n]))) for n in LY.PARAMS if np.any(ref[n])}
+    print(f"weight gradients H={H} D={D} {lengths}: " + " ".join(f"{k} {v:.1e}" for k, v in errs.items()), flush=True)
+    # (3 + g is rounded to fp32: at most 2^-23 of 3, against gradients of order 0.1 and more)
+    assert max(errs.values()) <= GRAD_TOL, errs
+
+
 def test_recompute_is_bitwise_the_stashed_backward(torch):
     layer, cu, Wb, xb, db, x, dout = _setup(torch, [200, 37, 513, 9], 4, 72, False, 5)
     kept = _run(torch, layer, x, dout, keep=True)
