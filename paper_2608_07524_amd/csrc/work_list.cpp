@@ -123,6 +123,11 @@ UnitList build_units(const dcp_attn_desc* d, int tile, int window_tile, bool key
   const bool reverse = d->causal && !keys_major;
   // sequence tiles and packed windows run as separate launches: each is
   // balanced over the dies on its own
+  // A window's heads read and write interleaved pieces of the same rows (144
+  // bytes each at head width 72, not whole cache lines), so neighbouring heads
+  // go to one die as far as every CU of every die still gets two workgroups.
+  const int64_t n_win = int64_t(out.window_starts.size() / kWindowWords);
+  const int32_t win_heads = int32_t(std::max<int64_t>(1, std::min<int64_t>(H, n_win * H / (2 * kNumCU))));
   for (int windows = 0; windows < 2; ++windows) {
     std::vector<std::vector<WorkUnit>> lists(kNumXcd);
     for (auto& l : lists) l.reserve(total / kNumXcd + size_t(cap) + 1);
@@ -130,23 +135,27 @@ UnitList build_units(const dcp_attn_desc* d, int tile, int window_tile, bool key
     for (const Group& g : groups) {
       if ((g.window >= 0) != (windows == 1)) continue;
       const int32_t s0 = cu[g.b], len = cu[g.b + 1] - cu[g.b];
-      for (int32_t h = 0; h < H; ++h) {
+      const int32_t hstep = g.window >= 0 ? win_heads : 1;
+      for (int32_t h = 0; h < H; h += hstep) {
         // the least-loaded die takes the chunk
         int x = 0;
         for (int i = 1; i < kNumXcd; ++i)
           if (load[i] < load[x]) x = i;
-        load[x] += g.work;
         std::vector<WorkUnit>& l = lists[size_t(x)];
         if (g.window >= 0) {
-          WorkUnit u{};
-          u.row0 = s0;
-          u.seq0 = s0;
-          u.seqlen = -g.window - 1;
-          u.rows = uint16_t(g.t_end);
-          u.head = uint16_t(h);
-          l.push_back(u);
+          for (int32_t hh = h; hh < std::min(H, h + hstep); ++hh) {
+            load[x] += g.work;
+            WorkUnit u{};
+            u.row0 = s0;
+            u.seq0 = s0;
+            u.seqlen = -g.window - 1;
+            u.rows = uint16_t(g.t_end);
+            u.head = uint16_t(hh);
+            l.push_back(u);
+          }
           continue;
         }
+        load[x] += g.work;
         for (int32_t i = g.t_begin; i < g.t_end; ++i) {
           const int32_t t = reverse ? g.t_end - 1 - (i - g.t_begin) : i;
           WorkUnit u{};
