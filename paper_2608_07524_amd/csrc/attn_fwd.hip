@@ -55,7 +55,8 @@ namespace {
 constexpr int kFwdBN = 64;
 // Ring depth: tile kt + kFwdStages - 1 streams in while tile kt is consumed.
 constexpr int kFwdStages = 4;
-static_assert(kFwdStages >= 3 && kWinFwdStages >= 3, "tiles kt and kt + 1 are read while kt + 2 lands");
+static_assert(kFwdStages >= 3, "tiles kt and kt + 1 are read while kt + 2 lands");
+static_assert(kWinFwdStages * kFwdBN >= kWinFwdWaves * 32, "the ring holds a whole window");
 constexpr int kFwdSplitStages = 6;  // with key streams (a step takes two tiles)
 constexpr float kRescaleSlack = 8.0f;  // log2 units
 constexpr float kNoMax = -1e30f;       // running max before any key
@@ -88,7 +89,7 @@ struct FwdShape {
 };
 
 template <int D, int NW, bool CAUSAL, bool PACKED, int STAGES, int KS>
-__global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const __bf16* __restrict__ q,
+__global__ __launch_bounds__(64 * NW, PACKED ? (D <= 72 ? 3 : 2) : 1) void attn_fwd_kernel(const __bf16* __restrict__ q,
                                                            const __bf16* __restrict__ k,
                                                            const __bf16* __restrict__ v, __bf16* __restrict__ o,
                                                            float* __restrict__ lse,
@@ -105,7 +106,7 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const __bf16* __restr
   constexpr int VBUF = DV::ELEMS;
   // as deep as asked, within the 160 KB of LDS
   constexpr int NST = STAGES * 2 * (KBUF + VBUF) <= 163840 ? STAGES : 163840 / (2 * (KBUF + VBUF));
-  static_assert(NST >= 3, "ring too shallow");
+  static_assert(NST >= (PACKED ? 2 : 3), "ring too shallow");
   constexpr int NI = DK::NI + DV::NI;  // copies per wavefront per tile
 
   __shared__ __attribute__((aligned(16))) __bf16 Ks[NST * KBUF];
@@ -141,25 +142,47 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const __bf16* __restr
   const int qi = wave_q0 + j;  // this lane's query
   // keys of this lane's sequence: [k_lo, k_hi)
   int k_lo = 0, k_hi = seqlen;
-  if (packed) window_bounds(window_starts + kWindowWords * (-u.seqlen - 1), min(qi, seqlen - 1), seqlen, k_lo, k_hi);
 
   // Q fragments (B operand of S^T): lane (g, j) holds query j,
   // columns 16*kd + 8*g .. +7.
   bf16x8 qf[NKD];
+  auto load_q = [&]() DCP_INLINE {
 #pragma unroll
-  for (int kd = 0; kd < NKD; ++kd) {
-    const int col = 16 * kd + 8 * g;
-    if (qw * 32 + j < u.rows && col < D) {
-      qf[kd] = *reinterpret_cast<const bf16x8*>(qh + int64_t(qi) * ts + col);
-    } else {
-      qf[kd] = bf16x8{};
+    for (int kd = 0; kd < NKD; ++kd) {
+      const int col = 16 * kd + 8 * g;
+      if (qw * 32 + j < u.rows && col < D) {
+        qf[kd] = *reinterpret_cast<const bf16x8*>(qh + int64_t(qi) * ts + col);
+      } else {
+        qf[kd] = bf16x8{};
+      }
     }
-  }
-
+  };
   // Settle the Q loads here: the tile copies below are invisible to the
   // compiler's wait tracking, so no later compiler-inserted wait may stand
   // for these loads inside the tile loop.
-  wait_vmcnt<0>();
+  if constexpr (!PACKED) {
+    load_q();
+    wait_vmcnt<0>();
+  } else {
+    // A window's key tiles, at most two, are copied at once, ahead of the
+    // loads of Q and of the window's mask: a window is little work (a few
+    // blocks for 73 KB of traffic), so its workgroup is one chain of memory
+    // latencies, and the launch is as fast as chains overlap.  One latency
+    // less and three workgroups per CU instead of two (no ring to advance:
+    // 150 registers, 47 KB of LDS): temporal pack 352 -> 267 us, 4.5 TB/s,
+    // where a plain copy reaches 4.8.
+    const int n0 = (seqlen + BN - 1) / BN;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+      if (t < n0) {
+        const int valid = min(BN, seqlen - t * BN);
+        DK::issue(&Ks[t * KBUF], kh + int64_t(t) * BN * ts, ts, valid, zero, zero, wave, lane);
+        DV::issue(&Vs[t * VBUF], vh + int64_t(t) * BN * ts, ts, valid, zero, v_pad, wave, lane);
+      }
+    load_q();
+    window_bounds(window_starts + kWindowWords * (-u.seqlen - 1), min(qi, seqlen - 1), seqlen, k_lo, k_hi);
+    wait_vmcnt<0>();
+  }
 
   const int key_end = CAUSAL ? min(seqlen, tile_q0 + u.rows) : seqlen;
   const int n_tiles = (key_end + BN - 1) / BN;
@@ -191,7 +214,7 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const __bf16* __restr
   const typename DK::FullOffsets fo_k = DK::full_offsets(ts, wave, lane);
   const typename DV::FullOffsets fo_v = DV::full_offsets(ts, wave, lane);
   const auto vskip = DV::template skip_masks<CPR>(wave, lane);
-  if constexpr (S::ONES_ROW) {
+  if constexpr (S::ONES_ROW && !PACKED) {
     for (int idx = tid; idx < NST * BN; idx += 64 * NW) {
       const int st = idx / BN, r = idx % BN;
       *reinterpret_cast<bf16x8*>(&Vs[st * VBUF + r * VSTR + S::VSKEW * (r / 16) + 8 * CPR]) =
@@ -597,15 +620,17 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const __bf16* __restr
     return;
   }
 
+  if constexpr (!PACKED) {
 #pragma unroll
-  for (int t = 0; t < PD; ++t)
-    if (t < n_tiles) issue_tile(t);
+    for (int t = 0; t < PD; ++t)
+      if (t < n_tiles) issue_tile(t);
+  }
   wait_for(0);
   __syncthreads();
 
   // A tile this wavefront has no work in: its copies, wait and barrier.
   auto idle = [&](int kt) DCP_INLINE {
-    if (kt + PD < n_tiles) issue_tile(kt + PD);
+    if (!PACKED && kt + PD < n_tiles) issue_tile(kt + PD);
     wait_for(kt + 1);
     __syncthreads();
   };
@@ -646,7 +671,7 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const __bf16* __restr
   // the first block of tile kt + 1, and the reads ahead take the two blocks
   // of tile kt + 1 (landed before tile kt began).
   auto tile = [&](int kt, auto mask_tag) DCP_INLINE {
-    if (kt + PD < n_tiles) issue_tile(kt + PD);
+    if (!PACKED && kt + PD < n_tiles) issue_tile(kt + PD);
     unsigned kb0 = (unsigned(kt) % NST) * KBUF + kr_off;
     unsigned kb1 = (unsigned(kt + 1) % NST) * KBUF + kr_off;
     unsigned vb0 = (unsigned(kt) % NST) * VBUF + tr_lane;

@@ -96,7 +96,7 @@ constexpr bool kBwdDqOneCopy = true;
 // shallower ring -- for the dK/dV pass also 32-query ring tiles -- so that
 // two workgroups share a CU; a window then spans at most that many rows.
 constexpr int kWinFwdWaves = 4;
-constexpr int kWinFwdStages = 3;
+constexpr int kWinFwdStages = 2;  // the whole window at once, three workgroups per CU
 constexpr int kWinDqWaves = 4;
 constexpr int kWinDqStages = 2;
 constexpr int kWinDkdvWaves = 4;
