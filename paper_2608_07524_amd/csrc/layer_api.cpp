@@ -8,9 +8,10 @@
 //   o  = attention(q, k, v) per sequence (the HIP kernels of this library),
 //   h  = x + o Wo,  y2 = RMSNorm(h; g2),  u = y2 Wup ([T, 4 hidden]),
 //   a  = GELU(u),   out = h + a Wdown.
-// The activations' GEMMs are plain library GEMMs (rocBLAS, bf16 inputs, fp32
-// compute); the weight gradients are formed together by layer_gemm.hip, the
-// norms and the activation are the kernels of layer.hip.  A forward with a
+// The projections are plain library GEMMs (rocBLAS, bf16 inputs, fp32 compute)
+// or, where several of them or one and what follows it are better done at once,
+// the kernels of layer_proj.hip; the weight gradients are formed together by
+// layer_gemm.hip, the norms and the activation are the kernels of layer.hip.  A forward with a
 // stash keeps every activation the backward needs; with no stash it keeps
 // nothing and the backward runs the forward again first (recomputation).
 #include <hip/hip_runtime.h>
@@ -180,6 +181,22 @@ int gemm(rocblas_handle hd, bool ta, bool tb, int64_t M, int64_t N, int64_t K, c
   return DCP_OK;
 }
 
+// Which projections layer_proj.hip takes.  It saves launches and passes over
+// memory; the library's main loop is faster once the contraction is long.  Library /
+// fused, us, at (hidden, tokens):
+//   Q, K, V    (1152, 300) 28 / 15, (1152, 16381) 175 / 145, (2048, 1000) 61 /
+//              39, (2048, 4000) 111 / 126, (3072, 1000) 89 / 66, (3072, 8192) 406 / 425
+//   W_up+GELU  (1152, 300) 16 / 17, (1152, 1000) 31 / 22, (1152, 16381) 237 /
+//              201, (2048, 1000) 48 / 51, (2048, 16000) 521 / 543
+//   W_down^T+GELU'  (1152, 300) 14 / 18, (1152, 1000) 27 / 23, (1152, 16381)
+//              249 / 221, (2048, 1000) 47 / 50, (2048, 16000) 522 / 563
+//   dY1        (1152, 1000) 29 / 39, (1152, 2500) 43 / 42, (1152, 16381) 185 /
+//              137, (2048, 4000) 127 / 135
+constexpr int64_t kProjHidden = 1536;
+inline bool fused_qkv(const Dims& d) { return d.h <= kProjHidden || d.T * d.h <= int64_t(4) << 20; }
+inline bool fused_gelu(const Dims& d) { return d.h <= kProjHidden && d.T >= 512; }
+inline bool fused_dy1(const Dims& d) { return d.h <= kProjHidden && d.T >= 2048; }
+
 int check_ptrs(std::initializer_list<const void*> ps, const char* what) {
   for (const void* p : ps)
     if (!p || reinterpret_cast<uintptr_t>(p) % 16) return fail(DCP_ERR_INVALID, "%s: null or not 16-byte aligned", what);
@@ -204,16 +221,28 @@ int forward(const dcp_layer_desc* L, const Dims& d, const dcp_layer_weights* w, 
             const Stash& s, void* attn_ws, size_t attn_ws_bytes, rocblas_handle hd, hipStream_t st) {
   const int64_t T = d.T, h = d.h;
   DCP_HIP(launch_rmsnorm_fwd(x, w->norm1, at(sb, s.y1), reinterpret_cast<float*>(at(sb, s.rstd1)), T, int(h), L->eps, st));
-  DCP_TRY(gemm(hd, false, false, T, h, h, at(sb, s.y1), w->wq, 0.f, at(sb, s.q), at(sb, s.q), false));
-  DCP_TRY(gemm(hd, false, false, T, h, h, at(sb, s.y1), w->wk, 0.f, at(sb, s.k), at(sb, s.k), false));
-  DCP_TRY(gemm(hd, false, false, T, h, h, at(sb, s.y1), w->wv, 0.f, at(sb, s.v), at(sb, s.v), false));
+  const void* y1 = at(sb, s.y1);
+  if (fused_qkv(d)) {
+    const Proj p{{y1, y1, y1}, {w->wq, w->wk, w->wv}, {at(sb, s.q), at(sb, s.k), at(sb, s.v)}, nullptr, nullptr, T, int(h),
+                 int(h), 1, 3, 0};
+    DCP_HIP(launch_proj(p, ProjEpilogue::kStore, st));
+  } else {
+    DCP_TRY(gemm(hd, false, false, T, h, h, y1, w->wq, 0.f, at(sb, s.q), at(sb, s.q), false));
+    DCP_TRY(gemm(hd, false, false, T, h, h, y1, w->wk, 0.f, at(sb, s.k), at(sb, s.k), false));
+    DCP_TRY(gemm(hd, false, false, T, h, h, y1, w->wv, 0.f, at(sb, s.v), at(sb, s.v), false));
+  }
   DCP_TRY(dcp_varlen_attn_fwd(L->attn, at(sb, s.q), at(sb, s.k), at(sb, s.v), at(sb, s.o),
                               reinterpret_cast<float*>(at(sb, s.lse)), attn_ws, attn_ws_bytes, st));
   DCP_TRY(gemm(hd, false, false, T, h, h, at(sb, s.o), w->wo, 1.f, x, at(sb, s.hres), false));
   DCP_HIP(launch_rmsnorm_fwd(at(sb, s.hres), w->norm2, at(sb, s.y2), reinterpret_cast<float*>(at(sb, s.rstd2)), T,
                              int(h), L->eps, st));
-  DCP_TRY(gemm(hd, false, false, T, 4 * h, h, at(sb, s.y2), w->w_up, 0.f, at(sb, s.u), at(sb, s.u), false));
-  DCP_HIP(launch_gelu_fwd(at(sb, s.u), at(sb, s.a), T * 4 * h, st));
+  if (fused_gelu(d)) {
+    const Proj p{{at(sb, s.y2)}, {w->w_up}, {at(sb, s.u)}, nullptr, at(sb, s.a), T, int(4 * h), int(h), 1, 1, 0};
+    DCP_HIP(launch_proj(p, ProjEpilogue::kGelu, st));
+  } else {
+    DCP_TRY(gemm(hd, false, false, T, 4 * h, h, at(sb, s.y2), w->w_up, 0.f, at(sb, s.u), at(sb, s.u), false));
+    DCP_HIP(launch_gelu_fwd(at(sb, s.u), at(sb, s.a), T * 4 * h, st));
+  }
   DCP_TRY(gemm(hd, false, false, T, h, 4 * h, at(sb, s.a), w->w_down, 1.f, at(sb, s.hres), out, false));
   return DCP_OK;
 }
@@ -292,8 +321,13 @@ extern "C" int dcp_layer_bwd(const dcp_layer_desc* L, const dcp_layer_weights* w
   const int64_t T = d.T, h = d.h;
   float* partial = reinterpret_cast<float*>(at(workspace, b.partial));
   // MLP: dA = dout Wdown^T; dU = dA * GELU'(U) (in place)
-  DCP_TRY(gemm(hd, false, true, T, 4 * h, h, dout, w->w_down, 0.f, at(workspace, b.da), at(workspace, b.da), false));
-  DCP_HIP(launch_gelu_bwd(at(sb, s.u), at(workspace, b.da), at(workspace, b.da), T * 4 * h, st));
+  if (fused_gelu(d)) {
+    const Proj p{{dout}, {w->w_down}, {at(workspace, b.da)}, at(sb, s.u), nullptr, T, int(4 * h), int(h), 1, 1, 0};
+    DCP_HIP(launch_proj(p, ProjEpilogue::kGeluGrad, st));
+  } else {
+    DCP_TRY(gemm(hd, false, true, T, 4 * h, h, dout, w->w_down, 0.f, at(workspace, b.da), at(workspace, b.da), false));
+    DCP_HIP(launch_gelu_bwd(at(sb, s.u), at(workspace, b.da), at(workspace, b.da), T * 4 * h, st));
+  }
   // dY2 = dU Wup^T (fp32); dH = dout + RMSNorm backward
   DCP_TRY(gemm(hd, false, true, T, h, 4 * h, at(workspace, b.da), w->w_up, 0.f, at(workspace, b.dy2),
                at(workspace, b.dy2), true));
@@ -308,9 +342,15 @@ extern "C" int dcp_layer_bwd(const dcp_layer_desc* L, const dcp_layer_weights* w
                               at(workspace, b.attn_b), b.stash - b.attn_b, st));
   // dY1 = dQ Wq^T + dK Wk^T + dV Wv^T (fp32)
   void* dY1 = at(workspace, b.dy1);
-  DCP_TRY(gemm(hd, false, true, T, h, h, at(workspace, b.dq), w->wq, 0.f, dY1, dY1, true));
-  DCP_TRY(gemm(hd, false, true, T, h, h, at(workspace, b.dk), w->wk, 1.f, dY1, dY1, true));
-  DCP_TRY(gemm(hd, false, true, T, h, h, at(workspace, b.dv), w->wv, 1.f, dY1, dY1, true));
+  if (fused_dy1(d)) {
+    const Proj p{{at(workspace, b.dq), at(workspace, b.dk), at(workspace, b.dv)}, {w->wq, w->wk, w->wv}, {dY1}, nullptr,
+                 nullptr, T, int(h), int(h), 3, 1, 0};
+    DCP_HIP(launch_proj(p, ProjEpilogue::kSumF32, st));
+  } else {
+    DCP_TRY(gemm(hd, false, true, T, h, h, at(workspace, b.dq), w->wq, 0.f, dY1, dY1, true));
+    DCP_TRY(gemm(hd, false, true, T, h, h, at(workspace, b.dk), w->wk, 1.f, dY1, dY1, true));
+    DCP_TRY(gemm(hd, false, true, T, h, h, at(workspace, b.dv), w->wv, 1.f, dY1, dY1, true));
+  }
   // every weight gradient in one launch: dWdown += A^T dout, dWup += Y2^T dU,
   // dWo += O^T dH, dW{q,k,v} += Y1^T d{Q,K,V}
   const int hi = int(h);

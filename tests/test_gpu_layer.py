@@ -109,6 +109,25 @@ def test_weight_gradients(torch, H, D, lengths):
     assert max(errs.values()) <= GRAD_TOL, errs
 
 
+# The projections' tiles are 192 features x 64 or (more than 256 tiles) 128
+# tokens, their slices 64 of the contraction.  Widths of one slice, of a slice
+# and a remainder, across a feature tile; tokens at and around the counts from
+# which GELU (512) and dY1 (2,048) are fused, and at tile edges; both tile
+# heights of every product.
+@pytest.mark.parametrize("H,D,lengths", [(1, 64, [512]), (1, 72, [511, 1]), (3, 72, [513]), (4, 72, [2047, 66]),
+                                         (2, 128, [1025, 1023]), (1, 72, [70] * 476), (16, 72, [300, 277])])
+def test_projections(torch, H, D, lengths):
+    layer, cu, Wb, xb, db, x, dout = _setup(torch, lengths, H, D, True, 51 + H)
+    out, dx, grads = _run(torch, layer, x, dout, keep=True)
+    ref_out, cache = LY.layer_forward(xb, Wb, cu, H, D, 1.0 / math.sqrt(D), True, 1e-6)
+    ref_dx, ref = LY.layer_backward(db, Wb, cache, cu, H, D, 1.0 / math.sqrt(D), True)
+    pairs = {"out": (I.bf16_to_f64(out), ref_out), "dx": (I.bf16_to_f64(dx), ref_dx)}
+    pairs.update({n: (grads[n].astype(np.float64), ref[n]) for n in LY.PARAMS})
+    errs = {n: float(np.max(np.abs(a - b)) / np.max(np.abs(b))) for n, (a, b) in pairs.items()}
+    print(f"projections H={H} D={D} T={len(x)}: " + " ".join(f"{k} {v:.1e}" for k, v in errs.items()), flush=True)
+    assert max(errs.values()) <= GRAD_TOL, errs
+
+
 def test_recompute_is_bitwise_the_stashed_backward(torch):
     layer, cu, Wb, xb, db, x, dout = _setup(torch, [200, 37, 513, 9], 4, 72, False, 5)
     kept = _run(torch, layer, x, dout, keep=True)
