@@ -2,9 +2,16 @@
 // exact attention the paper trains with, Sec. 4.1; block diagonal over the
 // packed sequences of Sec. 1).
 //
-// Three launches, no atomics, bitwise deterministic:
-//   1. bwd_delta:  -Delta = -rowsum(dO o O) and LSE*log2e per (row, head),
-//                  fp32.
+// Two passes, no atomics, bitwise deterministic:
+//   1. bwd_dq:     query-stationary, shaped like the forward.  One workgroup
+//                  per (query tile of 32*NW rows, head); each wavefront keeps
+//                  32 queries' Q and dO fragments, LSE, Delta and its dQ^T
+//                  accumulator in registers while K / V tiles stream through
+//                  LDS:
+//                    S^T = K Q^T,  dP^T = V dO^T       (A from LDS, B in regs)
+//                    dS^T = exp2(S^T*c - LSE*log2e) o (dP^T - Delta)
+//                    dQ^T += K^T dS^T                  (A via transposing reads,
+//                                                       B = dS^T from registers)
 //   2. bwd_dkdv:   key-stationary.  One workgroup per (key tile, head);
 //                  each wavefront keeps the K and V fragments of 32 keys
 //                  (at head width 128 V comes from an LDS copy instead, so
@@ -19,17 +26,10 @@
 //                    dV += P^T dO,  dK += dS^T Q       (B via transposing reads)
 //                  In the S / dP accumulators a lane holds one key and 16
 //                  queries: exactly the A-operand layout P^T and dS^T need.
-//   3. bwd_dq:     query-stationary, shaped like the forward.  One workgroup
-//                  per (query tile of 32*NW rows, head); each wavefront keeps
-//                  32 queries' Q and dO fragments, LSE, Delta and its dQ^T
-//                  accumulator in registers while K / V tiles stream through
-//                  LDS:
-//                    S^T = K Q^T,  dP^T = V dO^T       (A from LDS, B in regs)
-//                    dS^T = exp2(S^T*c - LSE*log2e) o (dP^T - Delta)
-//                    dQ^T += K^T dS^T                  (A via transposing reads,
-//                                                       B = dS^T from registers)
 // The dQ pass recomputes S and dP (two extra products) instead of adding
 // per-key-tile partial dQ into an fp32 accumulator with atomics.
+// -Delta = -rowsum(dO o O) and LSE*log2e (fp32 per row and head) come from a
+// pass of their own (bwd_delta) or, for small batches, from the dQ pass.
 #include <type_traits>
 
 #include "attn_common.h"
@@ -70,8 +70,32 @@ struct BwdShape {
   static_assert(OSTR % 16 == 8 && OSTR >= (KV16 ? NMB * 16 : NDB * 32), "one-copy stride");
 };
 
+// A lane's share of one row (null: zeros): columns 16*kd + 8*g .. +7.
+template <int D, int NKD>
+__device__ __forceinline__ void load_row(const __bf16* __restrict__ row, int g, bf16x8 (&f)[NKD]) {
+#pragma unroll
+  for (int kd = 0; kd < NKD; ++kd) {
+    const int col = 16 * kd + 8 * g;
+    f[kd] = row && col < D ? *reinterpret_cast<const bf16x8*>(row + col) : bf16x8{};
+  }
+}
+// -Delta = -sum over columns of dO o O of a lane's row, from both halves' shares
+// (pairwise dot products: as conversions and multiply-adds the sum held a CU's
+// matrix cores up for 0.6 us per workgroup at head width 128)
+template <int NKD>
+__device__ __forceinline__ float neg_delta(const bf16x8 (&dof)[NKD], const bf16x8 (&of)[NKD]) {
+  float sum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kd = 0; kd < NKD; ++kd)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      sum[e] = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{dof[kd][2 * e], dof[kd][2 * e + 1]},
+                                               bf16x2{of[kd][2 * e], of[kd][2 * e + 1]}, sum[e], false);
+  return -half_swap_sum((sum[0] + sum[1]) + (sum[2] + sum[3]));
+}
+
 // ---------------------------------------------------------------------------
-// 1. -Delta = -rowsum(dO o O) and LSE*log2e per (row, head), fp32 [H, T].
+// -Delta = -rowsum(dO o O) and LSE*log2e per (row, head), fp32 [H, T].
 // A workgroup takes kDeltaRows rows x up to kDeltaHeads heads: 16 lanes per
 // (row, head) pair, lane c covering columns 8c..8c+7.  Pairs are taken
 // row-major, so the heads of one token -- adjacent in memory -- are read
@@ -204,7 +228,7 @@ __device__ __forceinline__ void to_mfma16_layout(bf16x8& xv, bf16x8& yv) {
 }
 
 // ---------------------------------------------------------------------------
-// 2. dK, dV (key-stationary).
+// dK, dV (key-stationary).
 //
 // Each wavefront owns 32*KB keys: their K and V fragments (B operands of
 // S = Q K^T and dP = dO V^T) and their dK, dV accumulators stay in
@@ -235,11 +259,12 @@ __device__ __forceinline__ void to_mfma16_layout(bf16x8& xv, bf16x8& yv) {
 // fit two workgroups per CU the ring then holds Q and dO once, at the
 // row-read stride, and the transposing reads of dV and dK use that copy.
 template <int D, int KB, int NW, int BM, int NSTAGE, int WPE, bool CAUSAL, bool PACKED, bool FUSED, bool ONECOPY,
-          bool VLDS, int QS, int OSTR>
+          bool VLDS, int QS, int OSTR, bool DELTA>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) void attn_bwd_dkdv_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
-    const __bf16* __restrict__ dout, const float* __restrict__ lse2, const float* __restrict__ ndelta,
-    __bf16* __restrict__ dk, __bf16* __restrict__ dv, __bf16* __restrict__ dq, const __bf16* __restrict__ consts,
+    const __bf16* __restrict__ o, const __bf16* __restrict__ dout, const float* __restrict__ lse,
+    const float* __restrict__ lse2, const float* __restrict__ ndelta, __bf16* __restrict__ dk,
+    __bf16* __restrict__ dv, __bf16* __restrict__ dq, const __bf16* __restrict__ consts,
     const WorkUnit* __restrict__ units, const uint64_t* __restrict__ window_starts, int per_xcd, int H, int T,
     float scale, float scale_log2) {
   using S = BwdShape<D>;
@@ -259,7 +284,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   using DR = DmaTile<BM, RSTR / 8, CPR, NW>;
   using DT = DmaTile<BM, TSTR / 8, CPR, NW>;
   using DL = DmaVecPair<BM, NW>;
-  constexpr int NI = ONECOPY ? 2 * DR::NI + DL::NI : 2 * DR::NI + 2 * DT::NI + DL::NI;  // copies per wavefront per tile
+  static_assert(!DELTA || FUSED, "only whole windows form their Delta");
+  constexpr int NIL = DELTA ? 0 : DL::NI;
+  constexpr int NI = ONECOPY ? 2 * DR::NI + NIL : 2 * DR::NI + 2 * DT::NI + NIL;  // copies per wavefront per tile
   constexpr int RBUF = DR::ELEMS, TBUF = ONECOPY ? 0 : DT::ELEMS;
   constexpr int SSTR = S::RSTR;  // epilogue staging stride
   // fused dQ: the window's K rows for transposing reads, and dS^T
@@ -273,7 +300,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   __shared__ __attribute__((aligned(16))) __bf16 dOr[NSTAGE * RBUF];
   __shared__ __attribute__((aligned(16))) __bf16 Qt[ONECOPY ? 8 : NSTAGE * TBUF];
   __shared__ __attribute__((aligned(16))) __bf16 dOt[ONECOPY ? 8 : NSTAGE * TBUF];
-  __shared__ __attribute__((aligned(16))) float LV[NSTAGE * 2 * BM];  // LSE*log2e | -Delta
+  __shared__ __attribute__((aligned(16))) float LV[DELTA ? 2 * NKEY : NSTAGE * 2 * BM];  // LSE*log2e | -Delta
   __shared__ __attribute__((aligned(16))) __bf16 Kt[FUSED ? KTBUF : 8];
   __shared__ __attribute__((aligned(16))) __bf16 dSt[FUSED ? 2 * DSBUF : 8];
   // (VLDS) the tile's V rows, read 16 bytes per lane as B operands (an odd
@@ -317,23 +344,28 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
   // kb) + j of the tile, columns 16*kd + 8*g .. +7.  Keys past the sequence
   // end are zero; their dK, dV rows are never stored.
   bf16x8 kf[KB][NKD], vf[KB][NKD];
+  auto load_kv = [&]() DCP_INLINE {
 #pragma unroll
-  for (int kb = 0; kb < KB; ++kb) {
-    const int key = 32 * (KB * kw + kb) + j;
-    const bool ok = key < u.rows;
+    for (int kb = 0; kb < KB; ++kb) {
+      const int key = 32 * (KB * kw + kb) + j;
+      const bool ok = key < u.rows;
 #pragma unroll
-    for (int kd = 0; kd < NKD; ++kd) {
-      const int col = 16 * kd + 8 * g;
-      if (ok && col < D) {
-        kf[kb][kd] = *reinterpret_cast<const bf16x8*>(kh + int64_t(key_t0 + key) * ts + col);
-        if constexpr (!VLDS) vf[kb][kd] = *reinterpret_cast<const bf16x8*>(vh + int64_t(key_t0 + key) * ts + col);
-      } else {
-        kf[kb][kd] = bf16x8{};
-        if constexpr (!VLDS) vf[kb][kd] = bf16x8{};
+      for (int kd = 0; kd < NKD; ++kd) {
+        const int col = 16 * kd + 8 * g;
+        if (ok && col < D) {
+          kf[kb][kd] = *reinterpret_cast<const bf16x8*>(kh + int64_t(key_t0 + key) * ts + col);
+          if constexpr (!VLDS) vf[kb][kd] = *reinterpret_cast<const bf16x8*>(vh + int64_t(key_t0 + key) * ts + col);
+        } else {
+          kf[kb][kd] = bf16x8{};
+          if constexpr (!VLDS) vf[kb][kd] = bf16x8{};
+        }
       }
     }
+  };
+  if constexpr (!DELTA) {
+    load_kv();
+    wait_vmcnt<0>();  // settle the fragment loads before the first copy
   }
-  wait_vmcnt<0>();  // settle the fragment loads before the first copy
   // (fused) the window's keys, rows past its end zero; issued before the
   // first ring tile, so the first ring wait covers it
   if constexpr (FUSED) DKT::issue(Kt, kh + int64_t(key_t0) * ts, ts, u.rows, zero, zero, wave, lane);
@@ -385,7 +417,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
       if constexpr (!ONECOPY) DT::issue(&dOt[st * TBUF], ds, ts, valid, zero, zero, wave, lane);
     }
     // A query past the sequence end gets LSE = +inf, so its P is exactly 0.
-    DL::issue(&LV[st * 2 * BM], lseh + q0, ndh + q0, valid, finf, fzero, wave, lane);
+    if constexpr (!DELTA) DL::issue(&LV[st * 2 * BM], lseh + q0, ndh + q0, valid, finf, fzero, wave, lane);
   };
   // Waits until tile it+1 has landed (the tiles after it may stay in flight).
   auto wait_next = [&](int it) DCP_INLINE {
@@ -416,6 +448,23 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
       for (int nb = 0; nb < NMB; ++nb) dk16[kb][mb][nb] = dv16[kb][mb][nb] = f32x4{};
 
   for (int i = 0; i < NSTAGE - 1 && i < n_qt; ++i) issue_tile(i);
+  if constexpr (DELTA) {
+    load_kv();
+    // LSE*log2e and -Delta of the window's rows, formed here.  A row past the
+    // window's end gets LSE = +inf.
+    const int x = 32 * wave + j;
+    const int64_t off = int64_t(x) * ts;
+    bf16x8 of[NKD], dof[NKD];
+    load_row<D>(x < u.rows ? doh + off : nullptr, g, dof);
+    load_row<D>(x < u.rows ? o + int64_t(u.seq0) * ts + int64_t(h) * D + off : nullptr, g, of);
+    const float l = x < u.rows ? lse[int64_t(h) * T + u.seq0 + x] * kLog2e : INFINITY;
+    const float nd = neg_delta(dof, of);
+    if (g == 0) {
+      LV[x] = l;
+      LV[NKEY + x] = nd;
+    }
+    wait_vmcnt<0>();
+  }
   wait_next(-1);
   __syncthreads();
 
@@ -497,7 +546,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
     constexpr int MASK = decltype(mask_tag)::value;
     unsigned rb = st * RBUF + 32 * qb * RSTR + ar_off;
     unsigned tb = st * TBUF_R + 32 * qb * TSTR + tr_off;
-    unsigned lb = st * 2 * BM + 32 * qb + 4 * g;
+    unsigned lb = (DELTA ? qa : st * 2 * BM + 32 * qb) + 4 * g;
+    constexpr int kND = DELTA ? NKEY : BM;  // from a query's LSE to its -Delta
     unsigned vb = vl_off;
     // Opaque to the optimizer: each read below is then one of these bases
     // plus a constant, which folds into the instruction's offset field
@@ -514,7 +564,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
       f32x16 sv = f32x16{}, dpv;
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
-        const f32x4 t = lds_read_f32x4(LV3 + lb + BM + 8 * b);
+        const f32x4 t = lds_read_f32x4(LV3 + lb + kND + 8 * b);
 #pragma unroll
         for (int c = 0; c < 4; ++c) dpv[4 * b + c] = t[c];
       }
@@ -586,7 +636,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
     f32x16 nd;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-      const f32x4 t = lds_read_f32x4(LV3 + lb + BM + 8 * b);
+      const f32x4 t = lds_read_f32x4(LV3 + lb + kND + 8 * b);
 #pragma unroll
       for (int c = 0; c < 4; ++c) nd[4 * b + c] = t[c];
     }
@@ -831,7 +881,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
 }
 
 // ---------------------------------------------------------------------------
-// 3. dQ (query-stationary).
+// dQ (query-stationary).
 //
 // Each wavefront keeps 32 queries' Q and dO fragments (B operands), their
 // LSE*log2e and -Delta in registers while key tiles of BN rows stream
@@ -842,12 +892,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE))) 
 // reads use that copy.  KS > 1 (few tiles, see tile_parts): KS key streams x
 // NW / KS query groups, summed as in the dK/dV pass; two heads of width 128:
 // 4,096 tokens 125 -> 45 us, 16,384 tokens 521 -> 351.
-template <int D, int NW, int NSTAGE, bool CAUSAL, bool PACKED, bool ONECOPY, int KS, int NKB>
+template <int D, int NW, int NSTAGE, bool CAUSAL, bool PACKED, bool ONECOPY, int KS, int NKB, bool DELTA>
 __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ k, const __bf16* __restrict__ v,
-    const __bf16* __restrict__ dout, const float* __restrict__ lse2, const float* __restrict__ ndelta,
-    __bf16* __restrict__ dq, const __bf16* __restrict__ consts, const WorkUnit* __restrict__ units,
-    const uint64_t* __restrict__ window_starts, int per_xcd, int H, int T, float scale, float scale_log2) {
+    const __bf16* __restrict__ o, const __bf16* __restrict__ dout, const float* __restrict__ lse,
+    float* __restrict__ lse2, float* __restrict__ ndelta, __bf16* __restrict__ dq,
+    const __bf16* __restrict__ consts, const WorkUnit* __restrict__ units, const uint64_t* __restrict__ window_starts,
+    int per_xcd, int H, int T, float scale, float scale_log2) {
   using S = BwdShape<D>;
   constexpr int NKD = S::NKD, NDB = S::NDB, CPR = S::CPR;
   constexpr int KSTR = ONECOPY ? S::OSTR : S::DP + 8;  // K and V rows read 16 B per lane (and K transposed)
@@ -897,19 +948,20 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_kernel(
   if (packed)
     window_bounds(window_starts + kWindowWords * (-u.seqlen - 1), min(my_q, seqlen - 1), seqlen, k_lo, k_hi);
   bf16x8 qf[NKD], df[NKD];
-#pragma unroll
-  for (int kd = 0; kd < NKD; ++kd) {
-    const int col = 16 * kd + 8 * g;
-    if (q_ok && col < D) {
-      qf[kd] = *reinterpret_cast<const bf16x8*>(qh + int64_t(my_q) * ts + col);
-      df[kd] = *reinterpret_cast<const bf16x8*>(doh + int64_t(my_q) * ts + col);
-    } else {
-      qf[kd] = bf16x8{};
-      df[kd] = bf16x8{};
-    }
+  const int64_t q_off = int64_t(my_q) * ts;
+  load_row<D>(q_ok ? qh + q_off : nullptr, g, qf);
+  load_row<D>(q_ok ? doh + q_off : nullptr, g, df);
+  const int64_t lane_row = int64_t(h) * T + u.seq0 + my_q;
+  float lse_l2, ndlt;
+  if constexpr (DELTA) {
+    bf16x8 of[NKD];
+    load_row<D>(q_ok ? o + int64_t(u.seq0) * ts + int64_t(h) * D + q_off : nullptr, g, of);
+    lse_l2 = q_ok ? lse[lane_row] * kLog2e : INFINITY;
+    ndlt = neg_delta(df, of);
+  } else {
+    lse_l2 = q_ok ? lse2[lane_row] : INFINITY;
+    ndlt = q_ok ? ndelta[lane_row] : 0.f;
   }
-  const float lse_l2 = q_ok ? lse2[int64_t(h) * T + u.seq0 + my_q] : INFINITY;
-  const float ndlt = q_ok ? ndelta[int64_t(h) * T + u.seq0 + my_q] : 0.f;
   // -Delta as the initial dP^T accumulator, so the products yield
   // dP^T - Delta (at head width 128 the 16 registers it takes are not
   // spare: there the difference is taken per element instead).
@@ -918,6 +970,10 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_kernel(
 #pragma unroll
   for (int r = 0; r < 16; ++r) nd_init[r] = FOLD ? ndlt : 0.f;
   wait_vmcnt<0>();  // settle the fragment loads before the first copy
+  if (DELTA && q_ok && g == 0 && stream == 0) {  // for the dK/dV pass, which follows
+    lse2[lane_row] = lse_l2;
+    ndelta[lane_row] = ndlt;
+  }
 
   const int key_end = CAUSAL ? min(seqlen, tile_q0 + u.rows) : seqlen;
   const int n_tiles = (key_end + BN - 1) / BN;
@@ -1165,17 +1221,18 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_kernel(
 
 // QS query streams among NW wavefronts (QS 1: the pass's own shape); each unit
 // of a sequence-tile list becomes waves * QS / NW workgroups.
-template <int D, bool CAUSAL, bool PACKED, bool FUSED = false, int NW = 0, int QS = 1>
+template <int D, bool CAUSAL, bool PACKED, bool FUSED = false, int NW = 0, int QS = 1, bool DELTA = false>
 hipError_t launch_dkdv_list(const BwdArgs& a, const WorkUnit* units, int n_units) {
   constexpr DkdvShape sh = QS > 1 ? bwd_dkdv_split_shape(D, NW, QS) : PACKED ? bwd_dkdv_window_shape(D) : bwd_dkdv_shape(D);
   constexpr int PARTS = PACKED ? 1 : bwd_dkdv_shape(D).waves * QS / sh.waves;
   // (QS 4 at head width 128: only the minimal stride leaves room for two tiles)
   constexpr int OSTR = QS == 4 && D > 96 ? BwdShape<D>::DP + 8 : BwdShape<D>::OSTR;
   hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, sh.kb, sh.waves, sh.bm, sh.stages, sh.waves_per_eu, CAUSAL, PACKED, FUSED,
-                                           FUSED || sh.onecopy, sh.vlds, QS, OSTR>),
+                                           FUSED || sh.onecopy, sh.vlds, QS, OSTR, DELTA>),
                      dim3(n_units * PARTS), dim3(64 * sh.waves), 0, a.stream, static_cast<const __bf16*>(a.q),
                      static_cast<const __bf16*>(a.k), static_cast<const __bf16*>(a.v),
-                     static_cast<const __bf16*>(a.dout), a.lse2, a.ndelta, static_cast<__bf16*>(a.dk),
+                     static_cast<const __bf16*>(a.o), static_cast<const __bf16*>(a.dout), a.lse, a.lse2, a.ndelta,
+                     static_cast<__bf16*>(a.dk),
                      static_cast<__bf16*>(a.dv), static_cast<__bf16*>(a.dq), static_cast<const __bf16*>(a.consts), units,
                      static_cast<const uint64_t*>(a.window_starts), n_units / kNumXcd, a.n_heads, a.total_tokens,
                      a.scale, a.scale * kLog2e);
@@ -1183,13 +1240,13 @@ hipError_t launch_dkdv_list(const BwdArgs& a, const WorkUnit* units, int n_units
 }
 
 // KS key streams among NW wavefronts, NKB 32-key blocks each per ring tile.
-template <int D, int NW, int NS, bool CAUSAL, bool PACKED, int KS = 1, int NKB = 2>
+template <int D, int NW, int NS, bool CAUSAL, bool PACKED, bool DELTA, int KS = 1, int NKB = 2>
 hipError_t launch_dq_list(const BwdArgs& a, const WorkUnit* units, int n_units) {
   constexpr int PARTS = PACKED ? 1 : kBwdDqWaves * KS / NW;
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, NW, NS, CAUSAL, PACKED, kBwdDqOneCopy, KS, NKB>), dim3(n_units * PARTS),
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, NW, NS, CAUSAL, PACKED, kBwdDqOneCopy, KS, NKB, DELTA>), dim3(n_units * PARTS),
                      dim3(64 * NW), 0, a.stream, static_cast<const __bf16*>(a.q), static_cast<const __bf16*>(a.k),
-                     static_cast<const __bf16*>(a.v), static_cast<const __bf16*>(a.dout), a.lse2, a.ndelta,
-                     static_cast<__bf16*>(a.dq), static_cast<const __bf16*>(a.consts), units,
+                     static_cast<const __bf16*>(a.v), static_cast<const __bf16*>(a.o),
+                     static_cast<const __bf16*>(a.dout), a.lse, a.lse2, a.ndelta, static_cast<__bf16*>(a.dq), static_cast<const __bf16*>(a.consts), units,
                      static_cast<const uint64_t*>(a.qwindow_starts), n_units / kNumXcd, a.n_heads, a.total_tokens,
                      a.scale, a.scale * kLog2e);
   return hipGetLastError();
@@ -1205,52 +1262,73 @@ hipError_t launch_dkdv_tiles(const BwdArgs& a, const WorkUnit* units) {
   }
 }
 
-template <int D, bool CAUSAL>
+template <int D, bool CAUSAL, bool DELTA>
 hipError_t launch_dq_tiles(const BwdArgs& a, const WorkUnit* units) {
   constexpr int W = kBwdDqWaves;
   constexpr int NS = D > 96 ? kBwdDqStagesD128 : kBwdDqStages;  // (also two or three tiles of 128 keys when split)
   switch (tile_parts(a.n_qunits, CAUSAL)) {
     // (8 parts gain nothing over 4 here: 4,096 tokens 213 and 215 us per backward)
     case 8:
-    case 4: return launch_dq_list<D, W, NS, CAUSAL, false, 4, 1>(a, units, a.n_qunits);
-    case 2: return launch_dq_list<D, W, NS, CAUSAL, false, 2, 2>(a, units, a.n_qunits);
-    default: return launch_dq_list<D, W, NS, CAUSAL, false>(a, units, a.n_qunits);
+    case 4: return launch_dq_list<D, W, NS, CAUSAL, false, DELTA, 4, 1>(a, units, a.n_qunits);
+    case 2: return launch_dq_list<D, W, NS, CAUSAL, false, DELTA, 2, 2>(a, units, a.n_qunits);
+    default: return launch_dq_list<D, W, NS, CAUSAL, false, DELTA>(a, units, a.n_qunits);
   }
 }
 
-// Delta, then the dK/dV pass and the dQ pass, each over its sequence tiles
-// and then its packed windows (one launch per non-empty list).
-template <int D, bool CAUSAL>
-hipError_t launch_bwd_t(const BwdArgs& a) {
-  if (a.rows_end > 0) {
-    const dim3 grid(unsigned((a.rows_end + kDeltaRows - 1) / kDeltaRows),
-                    unsigned((a.n_heads + kDeltaHeads - 1) / kDeltaHeads));
-    hipLaunchKernelGGL((bwd_delta_kernel<D>), grid, dim3(kDeltaThreads), 0, a.stream,
-                       static_cast<const __bf16*>(a.dout), static_cast<const __bf16*>(a.o), a.lse, a.ndelta,
-                       a.lse2, a.rows_end, a.n_heads, a.total_tokens);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  const KernelEvents& ev = kernel_events();
-  const WorkUnit* units = static_cast<const WorkUnit*>(a.units);
-  const WorkUnit* qunits = static_cast<const WorkUnit*>(a.qunits);
-  hipError_t e = hipSuccess;
-  if (a.n_units + a.n_wunits > 0) {
+// The two passes, each over its sequence tiles and then its packed windows (one
+// launch per non-empty list).  With DELTA the dQ pass (and the windows whose dQ
+// the dK/dV pass computes) forms LSE*log2e and -Delta from O and dO and leaves
+// them for the dK/dV pass, so it goes first; otherwise both are in memory.
+template <int D, bool CAUSAL, bool DELTA>
+hipError_t launch_passes(const BwdArgs& a) {
+  constexpr bool FUSED = bwd_window_fused(D);
+  auto dq = [&]() {
+    const WorkUnit* qunits = static_cast<const WorkUnit*>(a.qunits);
+    hipError_t e = hipSuccess;
+    if (a.n_qunits > 0) e = launch_dq_tiles<D, CAUSAL, DELTA>(a, qunits);
+    // (windows with fused dQ: their dQ rows are written by the dK/dV pass)
+    if constexpr (!FUSED) {
+      constexpr int NS = D > 96 ? kBwdDqStagesD128 : kWinDqStages;
+      if (e == hipSuccess && a.n_wqunits > 0)
+        e = launch_dq_list<D, kWinDqWaves, NS, CAUSAL, true, DELTA>(a, qunits + a.n_qunits, a.n_wqunits);
+    }
+    return e;
+  };
+  auto dkdv = [&]() {
+    if (a.n_units + a.n_wunits == 0) return hipSuccess;
+    const KernelEvents& ev = kernel_events();
+    const WorkUnit* units = static_cast<const WorkUnit*>(a.units);
+    hipError_t e = hipSuccess;
     if (ev.begin) (void)hipEventRecord(ev.begin, a.stream);
     if (a.n_units > 0) e = launch_dkdv_tiles<D, CAUSAL>(a, units);
     if (e == hipSuccess && a.n_wunits > 0)
-      e = launch_dkdv_list<D, CAUSAL, true, bwd_window_fused(D)>(a, units + a.n_units, a.n_wunits);
+      e = launch_dkdv_list<D, CAUSAL, true, FUSED, 0, 1, FUSED && DELTA>(a, units + a.n_units, a.n_wunits);
     if (ev.end) (void)hipEventRecord(ev.end, a.stream);
-    if (e != hipSuccess) return e;
-  }
-  if (a.n_qunits > 0) e = launch_dq_tiles<D, CAUSAL>(a, qunits);
-  // (windows with fused dQ: their dQ rows were written by the dK/dV pass)
-  if constexpr (!bwd_window_fused(D)) {
-    constexpr int NS = D > 96 ? kBwdDqStagesD128 : kWinDqStages;
-    if (e == hipSuccess && a.n_wqunits > 0)
-      e = launch_dq_list<D, kWinDqWaves, NS, CAUSAL, true>(a, qunits + a.n_qunits, a.n_wqunits);
-  }
-  return e;
+    return e;
+  };
+  const hipError_t e = DELTA ? dq() : dkdv();
+  return e != hipSuccess ? e : DELTA ? dkdv() : dq();
+}
+
+template <int D, bool CAUSAL>
+hipError_t launch_bwd_t(const BwdArgs& a) {
+  // A batch of at most two rounds of workgroups has its Delta formed in the
+  // passes: one launch less, and dO is read there anyway.  Beyond that the sum
+  // lengthens every workgroup's start (a workgroup has its CU to itself) by as
+  // much as a pass at the copy rate takes.  Separate / formed in the passes,
+  // forward + backward: 4 short sequences 64.6 / 60.9 us, 4,096 tokens of 2 heads
+  // (32 units) 167 / 162, one frame of 3,600 (240) 324 / 318, 16,384 tokens of 2
+  // (128) 1,088 / 1,084; a 131k-token causal pack (16,960) 22.79 / 22.77 ms,
+  // documents of width 64 (14,640) 13.16 / 13.24 ms, thousands of windows 965 /
+  // 982 us.
+  if (a.n_qunits + a.n_wqunits <= 2 * kNumCU) return launch_passes<D, CAUSAL, true>(a);
+  const dim3 grid(unsigned((a.rows_end + kDeltaRows - 1) / kDeltaRows),
+                  unsigned((a.n_heads + kDeltaHeads - 1) / kDeltaHeads));
+  hipLaunchKernelGGL((bwd_delta_kernel<D>), grid, dim3(kDeltaThreads), 0, a.stream,
+                     static_cast<const __bf16*>(a.dout), static_cast<const __bf16*>(a.o), a.lse, a.ndelta, a.lse2,
+                     a.rows_end, a.n_heads, a.total_tokens);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? launch_passes<D, CAUSAL, false>(a) : e;
 }
 
 // Deterministic fill for profiling inputs: a 32-bit integer hash mapped to

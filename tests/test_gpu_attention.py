@@ -164,6 +164,17 @@ def test_tile_parts(torch, D, H, causal, lengths):
     _assert_close(got, ref, n, f"parts H={H} D={D} causal={causal}")
 
 
+# Batches of more than 512 units take Delta from a pass of its own, smaller ones
+# (every other test here) form it in the passes: many heads of tiles and windows,
+# and many windows beside tiles few enough to be cut.
+@pytest.mark.parametrize("D", [64, 72, 128])
+@pytest.mark.parametrize("H,causal,lengths", [(64, True, [300, 1, 129, 64, 0, 257, 600, 70, 90]),
+                                              (32, False, [300] + [100, 27] * 20)])
+def test_delta_pass(torch, D, H, causal, lengths):
+    got, ref, n = _run_case(torch, lengths, H, D, causal, seed=D + H)
+    _assert_close(got, ref, n, f"Delta pass H={H} D={D} causal={causal}")
+
+
 # A merge of streams whose running maxima lie far apart (and, causal, rows for
 # which only one stream has keys): K rows growing along the sequence.
 @pytest.mark.parametrize("D", [64, 72, 128])
