@@ -190,11 +190,23 @@ int gemm(rocblas_handle hd, bool ta, bool tb, int64_t M, int64_t N, int64_t K, c
 //              201, (2048, 1000) 48 / 51, (2048, 16000) 521 / 543
 //   W_down^T+GELU'  (1152, 300) 14 / 18, (1152, 1000) 27 / 23, (1152, 16381)
 //              249 / 221, (2048, 1000) 47 / 50, (2048, 16000) 522 / 563
+//   W_o, W_down with their residuals and dO: inside a step (cold operands) the
+//              library's products take 89, 225 and 68 us at (1152, 16381), not the
+//              59, 160 and 47 they take repeated, these stay within 5 %.  Whole
+//              step: (1152, 2500) 550 / 553, (1152, 4100) 746 / 757, (1152, 8192)
+//              1,258 / 1,227, (1440, 8192) 1,879 / 1,844, (1152, 16381) 2,397 /
+//              2,323; just past one round of tiles (512) the second is too empty,
+//              (1440, 10240; 640 tiles) 2,378 / 2,400
 //   dY1        (1152, 1000) 29 / 39, (1152, 2500) 43 / 42, (1152, 16381) 185 /
 //              137, (2048, 4000) 127 / 135
 constexpr int64_t kProjHidden = 1536;
+constexpr int64_t kPlainTokens = 6144;
 inline bool fused_qkv(const Dims& d) { return d.h <= kProjHidden || d.T * d.h <= int64_t(4) << 20; }
 inline bool fused_gelu(const Dims& d) { return d.h <= kProjHidden && d.T >= 512; }
+inline bool fused_plain(const Dims& d) {
+  const int64_t tiles = (d.T + 127) / 128 * ((d.h + 191) / 192);
+  return d.h <= kProjHidden && d.T >= kPlainTokens && (tiles <= 512 || tiles >= 768);
+}
 inline bool fused_dy1(const Dims& d) { return d.h <= kProjHidden && d.T >= 2048; }
 
 int check_ptrs(std::initializer_list<const void*> ps, const char* what) {
@@ -233,7 +245,14 @@ int forward(const dcp_layer_desc* L, const Dims& d, const dcp_layer_weights* w, 
   }
   DCP_TRY(dcp_varlen_attn_fwd(L->attn, at(sb, s.q), at(sb, s.k), at(sb, s.v), at(sb, s.o),
                               reinterpret_cast<float*>(at(sb, s.lse)), attn_ws, attn_ws_bytes, st));
-  DCP_TRY(gemm(hd, false, false, T, h, h, at(sb, s.o), w->wo, 1.f, x, at(sb, s.hres), false));
+  // A W + residual; hidden-wide output
+  auto add = [&](const void* a, const void* wt, const void* res, void* dst, int64_t K) -> int {
+    if (!fused_plain(d)) return gemm(hd, false, false, T, h, K, a, wt, 1.f, res, dst, false);
+    const Proj p{{a}, {wt}, {dst}, res, nullptr, T, int(h), int(K), 1, 1, 0};
+    DCP_HIP(launch_proj(p, ProjEpilogue::kResidual, st));
+    return DCP_OK;
+  };
+  DCP_TRY(add(at(sb, s.o), w->wo, x, at(sb, s.hres), h));
   DCP_HIP(launch_rmsnorm_fwd(at(sb, s.hres), w->norm2, at(sb, s.y2), reinterpret_cast<float*>(at(sb, s.rstd2)), T,
                              int(h), L->eps, st));
   if (fused_gelu(d)) {
@@ -243,7 +262,7 @@ int forward(const dcp_layer_desc* L, const Dims& d, const dcp_layer_weights* w, 
     DCP_TRY(gemm(hd, false, false, T, 4 * h, h, at(sb, s.y2), w->w_up, 0.f, at(sb, s.u), at(sb, s.u), false));
     DCP_HIP(launch_gelu_fwd(at(sb, s.u), at(sb, s.a), T * 4 * h, st));
   }
-  DCP_TRY(gemm(hd, false, false, T, h, 4 * h, at(sb, s.a), w->w_down, 1.f, at(sb, s.hres), out, false));
+  DCP_TRY(add(at(sb, s.a), w->w_down, at(sb, s.hres), out, 4 * h));
   return DCP_OK;
 }
 
@@ -336,7 +355,12 @@ extern "C" int dcp_layer_bwd(const dcp_layer_desc* L, const dcp_layer_weights* w
                              int(h), st));
   // attention block: dO = dH Wo^T; attention backward
   void* dO = at(workspace, b.dy1);  // dY1 is not needed yet: its space holds dO (bf16) first
-  DCP_TRY(gemm(hd, false, true, T, h, h, at(workspace, b.dh), w->wo, 0.f, dO, dO, false));
+  if (fused_plain(d)) {
+    const Proj p{{at(workspace, b.dh)}, {w->wo}, {dO}, nullptr, nullptr, T, int(h), int(h), 1, 1, 0};
+    DCP_HIP(launch_proj(p, ProjEpilogue::kStoreT, st));
+  } else {
+    DCP_TRY(gemm(hd, false, true, T, h, h, at(workspace, b.dh), w->wo, 0.f, dO, dO, false));
+  }
   DCP_TRY(dcp_varlen_attn_bwd(L->attn, dO, at(sb, s.o), reinterpret_cast<const float*>(at(sb, s.lse)), at(sb, s.q),
                               at(sb, s.k), at(sb, s.v), at(workspace, b.dq), at(workspace, b.dk), at(workspace, b.dv),
                               at(workspace, b.attn_b), b.stash - b.attn_b, st));

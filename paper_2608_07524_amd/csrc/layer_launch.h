@@ -37,8 +37,10 @@ hipError_t launch_wgrad(WgradBatch b, void* scratch, size_t scratch_bytes, hipSt
 // one sum over `pairs` operand pairs; outs > 1: pair s gives out[s] (pairs == 1).
 enum class ProjEpilogue {
   kStore,     // a w, bf16
+  kResidual,  // a w + aux, bf16
   kGelu,      // a w, bf16, and GELU of it to out2
   kGeluGrad,  // a w^T times GELU'(aux), bf16
+  kStoreT,    // a w^T, bf16
   kSumF32,    // sum of a w^T, fp32
 };
 constexpr int kProjMax = 3;

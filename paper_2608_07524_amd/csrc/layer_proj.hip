@@ -214,9 +214,9 @@ __global__ __launch_bounds__(kThreads, 2) void proj_kernel(Proj p) {
     for (int k = 0; k < TB; ++k) acc[i][k] = f32x16{};
 
   // Half the tokens of the output at a time, eight features per thread and item;
-  // what the epilogue reads (GELU's argument) is fetched before the products.
+  // what the epilogue reads (GELU's argument, the residual) is fetched before the products.
   constexpr int kItems = HALF * kWChunks / kThreads;
-  constexpr bool kAux = EPI == ProjEpilogue::kGeluGrad;
+  constexpr bool kAux = EPI == ProjEpilogue::kGeluGrad || EPI == ProjEpilogue::kResidual;
   bf16x8 aux[kAux ? 2 : 1][kItems];
   if constexpr (kAux) {
 #pragma unroll
@@ -309,7 +309,8 @@ __global__ __launch_bounds__(kThreads, 2) void proj_kernel(Proj p) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           float v = e < 4 ? lo[e] : hi[e - 4];
-          if constexpr (kAux) v *= gelu_grad(float(aux[hm][n][e]));
+          if constexpr (EPI == ProjEpilogue::kResidual) v += float(aux[hm][n][e]);
+          if constexpr (EPI == ProjEpilogue::kGeluGrad) v *= gelu_grad(float(aux[hm][n][e]));
           r[e] = __bf16(v);
         }
         *reinterpret_cast<bf16x8*>(static_cast<__bf16*>(p.out[pl.out]) + at) = r;
@@ -348,6 +349,8 @@ hipError_t launch_proj(const Proj& p, ProjEpilogue epi, hipStream_t s) {
   if (p.tokens == 0) return hipSuccess;
   switch (epi) {
     case ProjEpilogue::kStore: return launch<false, ProjEpilogue::kStore>(p, s);
+    case ProjEpilogue::kResidual: return launch<false, ProjEpilogue::kResidual>(p, s);
+    case ProjEpilogue::kStoreT: return launch<true, ProjEpilogue::kStoreT>(p, s);
     case ProjEpilogue::kGelu: return launch<false, ProjEpilogue::kGelu>(p, s);
     case ProjEpilogue::kGeluGrad: return launch<true, ProjEpilogue::kGeluGrad>(p, s);
     default: return launch<true, ProjEpilogue::kSumF32>(p, s);
