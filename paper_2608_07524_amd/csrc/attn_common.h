@@ -148,6 +148,54 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 0xF) | (0x7 << 4) | (0xF << 8) | ((N >> 4) << 14));
 }
 
+// Direct global -> LDS copies (global_load_lds): lane i's 16 (or 4) bytes, at
+// `g` or at `base` + its byte offset `off`, land in LDS at `lds` + 16*i (4*i).
+// Completion is tracked by vmcnt only.  M0 carries the LDS address and is
+// written by nothing else in these kernels.
+// Two waits the hardware does not insert, nor the compiler inside inline
+// assembly: one wait state between the write of M0 and the copy (s_nop 0, or a
+// copy may use the previous LDS address), and five between a vector
+// instruction's write of the scalar base and the copy (or it may use the
+// register's previous value): a base goes through copy_base first.
+__device__ __forceinline__ uint64_t copy_base(const void* p) {
+  // (readfirstlane returns a signed int: both halves go through uint32_t
+  // so the low word is zero-extended, never sign-extended into the high one)
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a >> 32)));
+  const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a)));
+  uint64_t base = (uint64_t(hi) << 32) | uint64_t(lo);
+  asm volatile("s_nop 4" : "+s"(base));
+  return base;
+}
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+  return __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(p)));  // low 32 bits = LDS offset
+}
+__device__ __forceinline__ void lds_copy16(uint32_t lds, uint64_t g) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds), "v"(g) : "memory");
+}
+__device__ __forceinline__ void lds_copy16(uint32_t lds, uint32_t off, uint64_t base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(lds), "v"(off), "s"(base)
+               : "memory");
+}
+__device__ __forceinline__ void lds_copy4(uint32_t lds, uint64_t g) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(lds), "v"(g) : "memory");
+}
+// The copies of the lanes in `mask` only.
+__device__ __forceinline__ void lds_copy16_masked(uint32_t lds, uint32_t off, uint64_t base, uint64_t mask) {
+  uint64_t saved;
+  asm volatile(
+      "s_mov_b32 m0, %2\n\t"
+      "s_mov_b64 %0, exec\n\t"
+      "s_mov_b64 exec, %1\n\t"
+      "global_load_lds_dwordx4 %3, %4\n\t"
+      "s_mov_b64 exec, %0"
+      : "=&s"(saved)
+      : "s"(mask), "s"(lds), "v"(off), "s"(base)
+      : "memory");
+}
+
 // Direct global -> LDS copy of one ROWS-row tile (gfx950
 // global_load_lds_dwordx4: each lane moves 16 bytes, a wavefront fills 64
 // consecutive 16-byte LDS slots, no registers involved).  In LDS, slot
@@ -220,21 +268,11 @@ struct DmaTile {
   // its scalar-base form).
   __device__ __forceinline__ static void issue_full(__bf16* lds_tile, const __bf16* src, const FullOffsets& fo,
                                                     int wave) {
-    // (readfirstlane returns a signed int: both halves go through uint32_t
-    // so the low word is zero-extended, never sign-extended into the high one)
-    const uint64_t a = reinterpret_cast<uint64_t>(src);
-    const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a >> 32)));
-    const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a)));
-    const uint64_t base = (uint64_t(hi) << 32) | uint64_t(lo);
+    const uint64_t base = copy_base(src);
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int t = min(wave + NW * i, NINS - 1);
-      const uint32_t m0 = __builtin_amdgcn_readfirstlane(
-          static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds_tile + dst(t))));
-      asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
-                   :
-                   : "s"(m0), "v"(fo.off[i]), "s"(base)
-                   : "memory");
+      lds_copy16(lds_addr(lds_tile + dst(t)), fo.off[i], base);
     }
   }
 
@@ -258,25 +296,11 @@ struct DmaTile {
   template <int SKIP>
   __device__ __forceinline__ static void issue_full_skip(__bf16* lds_tile, const __bf16* src, const FullOffsets& fo,
                                                          const SkipMasks<SKIP>& sm, int wave) {
-    const uint64_t a = reinterpret_cast<uint64_t>(src);
-    const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a >> 32)));
-    const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(a)));
-    const uint64_t base = (uint64_t(hi) << 32) | uint64_t(lo);
+    const uint64_t base = copy_base(src);
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int t = min(wave + NW * i, NINS - 1);
-      const uint32_t m0 = __builtin_amdgcn_readfirstlane(
-          static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds_tile + dst(t))));
-      uint64_t saved;
-      asm volatile(
-          "s_mov_b64 %0, exec\n\t"
-          "s_mov_b64 exec, %1\n\t"
-          "s_mov_b32 m0, %2\n\t"
-          "global_load_lds_dwordx4 %3, %4\n\t"
-          "s_mov_b64 exec, %0"
-          : "=&s"(saved)
-          : "s"(sm.m[i]), "s"(m0), "v"(fo.off[i]), "s"(base)
-          : "memory");
+      lds_copy16_masked(lds_addr(lds_tile + dst(t)), fo.off[i], base, sm.m[i]);
     }
   }
 
@@ -286,16 +310,9 @@ struct DmaTile {
   // for it right away, which defeats copying ahead.  The callers' explicit
   // vmcnt waits and barriers order it instead; callers also settle their
   // own earlier vector loads before the first copy, so that no wait the
-  // compiler inserts later stands for a load it tracks.  M0 is written here
-  // and used by nothing else in these kernels (checked in the generated
-  // code: no other M0 reader).
+  // compiler inserts later stands for a load it tracks.
   __device__ __forceinline__ static void dma16(const __bf16* g, __bf16* lds_base) {
-    const uint32_t m0 = __builtin_amdgcn_readfirstlane(
-        static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds_base)));  // low 32 bits = LDS offset
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
-                 :
-                 : "s"(m0), "v"(reinterpret_cast<uint64_t>(g))
-                 : "memory");
+    lds_copy16(lds_addr(lds_base), reinterpret_cast<uint64_t>(g));
   }
 };
 
@@ -320,12 +337,7 @@ struct DmaVecPair {
       const bool second = e >= N;
       const int idx = second ? e - N : e;
       const float* g = idx < valid ? (second ? b : a) + idx : (second ? fill_b : fill_a);
-      const uint32_t m0 = __builtin_amdgcn_readfirstlane(
-          static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds_vec + 64 * t)));
-      asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off"
-                   :
-                   : "s"(m0), "v"(reinterpret_cast<uint64_t>(g))
-                   : "memory");
+      lds_copy4(lds_addr(lds_vec + 64 * t), reinterpret_cast<uint64_t>(g));
     }
   }
 };

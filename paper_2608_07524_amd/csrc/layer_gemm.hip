@@ -68,31 +68,25 @@ struct Operand {
   }
   // Copies the slice starting at token t0, all of whose rows exist.
   __device__ __forceinline__ void issue_full(__bf16* lds, int64_t t0, int wave) const {
-    const uint64_t base = reinterpret_cast<uint64_t>(src + t0 * ld);
+    const uint64_t base = copy_base(src + t0 * ld);
 #pragma unroll
     for (int i = 0; i < kCopies; ++i) {
-      asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
-                   :
-                   : "s"(lds_at(lds, i, wave)), "v"(off[i]), "s"(base)
-                   : "memory");
+      lds_copy16(lds_at(lds, i, wave), off[i], base);
     }
   }
   // The same with rows from `tokens` on read as zero.
   __device__ __forceinline__ void issue_tail(__bf16* lds, int64_t t0, int64_t tokens, int wave, int lane) const {
-    const uint64_t base = reinterpret_cast<uint64_t>(src + t0 * ld);
+    const uint64_t base = copy_base(src + t0 * ld);
 #pragma unroll
     for (int i = 0; i < kCopies; ++i) {
       int c;
       const int r = row_of(i, wave, lane, c);
       const uint64_t g = t0 + r < tokens ? base + off[i] : reinterpret_cast<uint64_t>(zero_chunk);
-      asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
-                   :
-                   : "s"(lds_at(lds, i, wave)), "v"(g)
-                   : "memory");
+      lds_copy16(lds_at(lds, i, wave), g);
     }
   }
   __device__ __forceinline__ static uint32_t lds_at(__bf16* lds, int i, int wave) {
-    return __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds + 512 * (wave + 4 * i))));
+    return lds_addr(lds + 512 * (wave + 4 * i));
   }
 };
 

@@ -30,16 +30,6 @@ constexpr int kWChunks = kFT / 8;  // 16-byte chunks per LDS row of a [K, N] sli
 
 __device__ __attribute__((aligned(16))) const uint32_t zero_chunk[4] = {0, 0, 0, 0};
 
-__device__ __forceinline__ uint32_t lds_addr(__bf16* p) {
-  return __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(p)));
-}
-__device__ __forceinline__ void copy16(uint32_t lds, uint32_t off, uint64_t base) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(off), "s"(base) : "memory");
-}
-__device__ __forceinline__ void copy16(uint32_t lds, uint64_t g) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds), "v"(g) : "memory");
-}
-
 // A slice of ROWS rows x 64 contiguous contraction elements.  LDS rows are 128
 // bytes, chunk c of row r in slot c ^ (r / 2 % 8): 16 consecutive rows read at
 // one chunk then cover all banks.
@@ -59,14 +49,14 @@ struct RowSlice {
     }
   }
   __device__ __forceinline__ void issue(__bf16* lds, const __bf16* src, int k_left, int wave) const {
-    const uint64_t base = reinterpret_cast<uint64_t>(src);
+    const uint64_t base = copy_base(src);
     if (k_left >= kBK) {
 #pragma unroll
-      for (int i = 0; i < N; ++i) copy16(lds_addr(lds + 512 * (wave + 4 * i)), off[i], base);
+      for (int i = 0; i < N; ++i) lds_copy16(lds_addr(lds + 512 * (wave + 4 * i)), off[i], base);
     } else {
 #pragma unroll
       for (int i = 0; i < N; ++i)
-        copy16(lds_addr(lds + 512 * (wave + 4 * i)),
+        lds_copy16(lds_addr(lds + 512 * (wave + 4 * i)),
                8 * chunk < k_left ? base + off[i] : reinterpret_cast<uint64_t>(zero_chunk));
     }
   }
@@ -95,16 +85,16 @@ struct ColSlice {
     }
   }
   __device__ __forceinline__ void issue(__bf16* lds, const __bf16* src, int k_left, int wave, int lane) const {
-    const uint64_t base = reinterpret_cast<uint64_t>(src);
+    const uint64_t base = copy_base(src);
     if (k_left >= kBK) {
 #pragma unroll
-      for (int i = 0; i < N; ++i) copy16(lds_addr(lds + 512 * (wave + 4 * i)), off[i], base);
+      for (int i = 0; i < N; ++i) lds_copy16(lds_addr(lds + 512 * (wave + 4 * i)), off[i], base);
     } else {
 #pragma unroll
       for (int i = 0; i < N; ++i) {
         int c;
         const int r = row_of(i, wave, lane, c);
-        copy16(lds_addr(lds + 512 * (wave + 4 * i)),
+        lds_copy16(lds_addr(lds + 512 * (wave + 4 * i)),
                r < k_left ? base + off[i] : reinterpret_cast<uint64_t>(zero_chunk));
       }
     }

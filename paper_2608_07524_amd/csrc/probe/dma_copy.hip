@@ -20,7 +20,7 @@ __global__ __launch_bounds__(kThreads) void dma_copy_kernel(const uint8_t* __res
     const uint8_t* g = src + c * kChunk + wave * 1024 + lane * 16;
     const uint32_t m0 =
         __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(buf + wave * 1024)));
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_waitcnt vmcnt(0)"
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_waitcnt vmcnt(0)"
                  :
                  : "s"(m0), "v"(reinterpret_cast<uint64_t>(g))
                  : "memory");
