@@ -108,6 +108,7 @@ int dcp_varlen_attn_bwd_workspace_size(const dcp_attn_desc* desc, size_t* bytes)
  *   o          bf16 [T, H, D] output (rows of sequences only).
  *   lse        fp32 [H, T] output (rows of sequences only).
  *   workspace  device scratch of at least the queried size.
+ * Outputs do not overlap inputs or each other, except that o may be q's buffer.
  */
 int dcp_varlen_attn_fwd(const dcp_attn_desc* desc, const void* q, const void* k, const void* v,
                         void* o, float* lse, void* workspace, size_t workspace_bytes, void* stream);
@@ -125,7 +126,9 @@ int dcp_varlen_attn_fwd(const dcp_attn_desc* desc, const void* q, const void* k,
  *                 query-stationary workgroups (or, for packed windows at head
  *                 widths up to 96, by the window's dK/dV workgroup), so every
  *                 gradient is written once and is bitwise reproducible.
- * The call uses the same desc (scale, causal) as the forward.
+ * The call uses the same desc (scale, causal) as the forward.  Outputs do not
+ * overlap inputs or each other, except that dq may be q's or dout's buffer and
+ * one of the three o's (a small batch then takes one launch more).
  */
 int dcp_varlen_attn_bwd(const dcp_attn_desc* desc, const void* dout, const void* o, const float* lse,
                         const void* q, const void* k, const void* v, void* dq, void* dk, void* dv,

@@ -31,6 +31,7 @@
 // -Delta = -rowsum(dO o O) and LSE*log2e (fp32 per row and head) come from a
 // pass of their own (bwd_delta) or, for small batches, from the dQ pass.
 #include <type_traits>
+#include <utility>
 
 #include "attn_common.h"
 #include "attn_launch.h"
@@ -1310,6 +1311,19 @@ hipError_t launch_passes(const BwdArgs& a) {
   return e != hipSuccess ? e : DELTA ? dkdv() : dq();
 }
 
+// Whether a gradient shares storage with something the backward reads.
+bool grads_share_inputs(const BwdArgs& a) {
+  const size_t rows = size_t(a.n_heads) * size_t(a.total_tokens), bytes = rows * size_t(a.head_dim) * 2;
+  const std::pair<const void*, size_t> reads[] = {{a.q, bytes},    {a.k, bytes}, {a.v, bytes},
+                                                  {a.dout, bytes}, {a.o, bytes}, {a.lse, rows * sizeof(float)}};
+  for (const void* g : {a.dq, a.dk, a.dv})
+    for (const auto& [p, n] : reads) {
+      const uintptr_t x = reinterpret_cast<uintptr_t>(g), y = reinterpret_cast<uintptr_t>(p);
+      if (x < y + n && y < x + bytes) return true;
+    }
+  return false;
+}
+
 template <int D, bool CAUSAL>
 hipError_t launch_bwd_t(const BwdArgs& a) {
   // A batch of at most two rounds of workgroups has its Delta formed in the
@@ -1320,8 +1334,11 @@ hipError_t launch_bwd_t(const BwdArgs& a) {
   // (32 units) 167 / 162, one frame of 3,600 (240) 324 / 318, 16,384 tokens of 2
   // (128) 1,088 / 1,084; a 131k-token causal pack (16,960) 22.79 / 22.77 ms,
   // documents of width 64 (14,640) 13.16 / 13.24 ms, thousands of windows 965 /
-  // 982 us.
-  if (a.n_qunits + a.n_wqunits <= 2 * kNumCU) return launch_passes<D, CAUSAL, true>(a);
+  // 982 us.  dQ is then written before the dK/dV pass reads Q and dO, and O and
+  // LSE are read until the end: a gradient in the storage of one of them takes
+  // the separate pass, after which O and LSE are done with and dQ comes last,
+  // each workgroup's rows after it has read them.
+  if (a.n_qunits + a.n_wqunits <= 2 * kNumCU && !grads_share_inputs(a)) return launch_passes<D, CAUSAL, true>(a);
   const dim3 grid(unsigned((a.rows_end + kDeltaRows - 1) / kDeltaRows),
                   unsigned((a.n_heads + kDeltaHeads - 1) / kDeltaHeads));
   hipLaunchKernelGGL((bwd_delta_kernel<D>), grid, dim3(kDeltaThreads), 0, a.stream,

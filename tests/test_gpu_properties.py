@@ -113,6 +113,36 @@ def test_per_call_queue_deeper_than_staging_ring(torch):
             assert torch.equal(x, y), name
 
 
+# Sequence tiles cut into parts, tiles beside packed windows (dQ from the windows'
+# own pass, or fused), and more units than the passes form their Delta for.
+@pytest.mark.parametrize("D,H,causal,lengths", [(64, 2, True, [700, 1, 300]), (72, 2, False, [5, 17, 40, 3, 700, 60]),
+                                                (128, 2, False, [100, 27, 900, 60, 60]), (128, 90, True, [257, 600, 300])])
+@pytest.mark.parametrize("dq_in,dk_in", [("q", "o"), ("dout", None), ("o", None)])
+def test_outputs_in_input_storage(torch, D, H, causal, lengths, dq_in, dk_in):
+    """dq in q's, dout's or o's buffer (and dk in o's), o in q's: the results
+    of separate buffers.  (The forward bit for bit; in the backward another
+    launch may form Delta, so within the parity bounds.)"""
+    import paper_2608_07524_amd as P
+    from gpu_util import GRAD_TOL
+    rng = np.random.default_rng(12)
+    cu = I.cu_from_lengths(lengths)
+    scale = 1 / math.sqrt(D)
+    bits = I.tensors(rng, int(cu[-1]), H, D)
+    ref = _outputs(torch, bits, cu, scale, causal)
+    t = dict(zip(("q", "k", "v", "dout"), (to_device(torch, b) for b in bits)))
+    o = t["q"].clone()
+    o, lse = P.varlen_attn_fwd(o, t["k"], t["v"], cu, scale, causal, out=o)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_bits(o), ref[0]) and np.array_equal(lse.cpu().numpy(), ref[1])
+    t["o"] = o
+    got = P.varlen_attn_bwd(t["dout"], o, lse, t["q"], t["k"], t["v"], cu, scale, causal, dq=t[dq_in],
+                            dk=t[dk_in] if dk_in else None)
+    torch.cuda.synchronize()
+    for x, y in zip(got, ref[2:]):
+        a, b = I.bf16_to_f64(to_bits(x)), I.bf16_to_f64(y)
+        assert np.max(np.abs(a - b)) <= GRAD_TOL * np.max(np.abs(b))
+
+
 @pytest.mark.parametrize("causal", [False, True])
 def test_position_in_pack_invariance(torch, causal):
     """A sequence's outputs do not depend on where it sits in the pack or
