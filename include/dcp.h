@@ -418,7 +418,8 @@ typedef struct {
   const void *norm1, *wq, *wk, *wv, *wo, *norm2, *w_up, *w_down;
 } dcp_layer_weights;
 
-/* fp32 device gradients of the same shapes; the backward adds into them. */
+/* fp32 device gradients of the same shapes; the backward adds into them.
+ * Weights may share a buffer, and so may their gradients (which then add up). */
 typedef struct {
   float *norm1, *wq, *wk, *wv, *wo, *norm2, *w_up, *w_down;
 } dcp_layer_grads;

@@ -273,10 +273,33 @@ __global__ __launch_bounds__(kThreads) void wgrad_reduce_kernel(WgradBatch batch
     if (row0 + e < pr.m) pr.c[int64_t(row0 + e) * pr.n + col] += sum[e];
 }
 
+// Whether two problems add into the same memory (weights that share a gradient).
+bool share_output(const WgradBatch& b) {
+  for (const WgradProblem& p : b.p)
+    for (const WgradProblem* q = b.p; q != &p; ++q) {
+      const uintptr_t x = reinterpret_cast<uintptr_t>(p.c), y = reinterpret_cast<uintptr_t>(q->c);
+      if (x < y + sizeof(float) * size_t(q->m) * size_t(q->n) && y < x + sizeof(float) * size_t(p.m) * size_t(p.n))
+        return true;
+    }
+  return false;
+}
+
 }  // namespace
 
 hipError_t launch_wgrad(WgradBatch b, void* scratch, size_t scratch_bytes, hipStream_t s) {
   if (b.tokens == 0) return hipSuccess;
+  // Workgroups of one launch add to C without atomics, so problems with a common
+  // C run one after another (problems without rows or columns have no tiles).
+  if (share_output(b)) {
+    for (const WgradProblem& p : b.p) {
+      WgradBatch one{};
+      one.p[0] = p;
+      one.tokens = b.tokens;
+      const hipError_t e = launch_wgrad(one, scratch, scratch_bytes, s);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
   b.n_tiles = 0;
   for (WgradProblem& p : b.p) {
     p.tile0 = b.n_tiles;

@@ -109,6 +109,27 @@ def test_weight_gradients(torch, H, D, lengths):
     assert max(errs.values()) <= GRAD_TOL, errs
 
 
+# Matrices that share one gradient buffer: it receives the sum, whether the
+# tokens are split over workgroups (few tiles) or not.
+@pytest.mark.parametrize("H,D,lengths", [(3, 64, [600, 141]), (16, 72, [33, 32])])
+def test_shared_gradient_buffer(torch, H, D, lengths):
+    from paper_2608_07524_amd import _native as N
+    layer, cu, Wb, xb, db, x, dout = _setup(torch, lengths, H, D, True, 41 + H)
+    shared = layer.grads["wq"]
+    layer.grads["wk"] = layer.grads["wv"] = shared
+    layer.grads["w_down"] = layer.grads["w_up"]  # (one buffer, two shapes)
+    layer.g = N.LayerWeightsC(*[layer.grads[n].data_ptr() for n in N.LAYER_PARAMS])
+    layer.fwd(x)
+    layer.bwd(x, dout)
+    torch.cuda.synchronize()
+    _, cache = LY.layer_forward(xb, Wb, cu, H, D, 1.0 / math.sqrt(D), True, 1e-6)
+    _, ref = LY.layer_backward(db, Wb, cache, cu, H, D, 1.0 / math.sqrt(D), True)
+    want = {"wq": ref["wq"] + ref["wk"] + ref["wv"], "w_up": ref["w_up"] + ref["w_down"].reshape(ref["w_up"].shape),
+            "wo": ref["wo"]}
+    errs = {n: float(np.max(np.abs(layer.grads[n].cpu().numpy() - w)) / np.max(np.abs(w))) for n, w in want.items()}
+    assert max(errs.values()) <= GRAD_TOL, errs
+
+
 # The projections' tiles are 192 features x 64 or (more than 256 tiles) 128
 # tokens, their slices 64 of the contraction.  Widths of one slice, of a slice
 # and a remainder, across a feature tile; tokens at and around the counts from
