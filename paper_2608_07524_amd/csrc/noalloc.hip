@@ -56,16 +56,21 @@ extern "C" int dcp_varlen_attn_fwd_noalloc(const dcp_attn_desc* desc, const void
   int st = validate_desc(desc);
   if (st) return st;
   if ((st = check_fwd_tensors(q, k, v, o, lse))) return st;
+  // constants | units | window masks, each part 256-byte aligned
   UnitList units;
+  const size_t units_at = kConstBytes;
+  size_t windows_at = 0, need = 0;
   try {
-    units = build_pass(desc, kPassFwd);
+    // a list that does not fit gets the layout with the least padding
+    for (const bool heads_together : {true, false}) {
+      units = build_pass(desc, kPassFwd, heads_together);
+      windows_at = units_at + align_up(std::max<size_t>(1, units.units.size()) * sizeof(WorkUnit));
+      need = windows_at + align_up(std::max<size_t>(1, units.window_starts.size()) * sizeof(uint64_t));
+      if (need <= kScratchBytes) break;
+    }
   } catch (const std::bad_alloc&) {
     return fail(DCP_ERR_INVALID, "out of host memory building the work list");
   }
-  // constants | units | window masks, each part 256-byte aligned
-  const size_t units_at = kConstBytes;
-  const size_t windows_at = units_at + align_up(std::max<size_t>(1, units.units.size()) * sizeof(WorkUnit));
-  const size_t need = windows_at + align_up(std::max<size_t>(1, units.window_starts.size()) * sizeof(uint64_t));
   if (need > kScratchBytes)
     return fail(DCP_ERR_WORKSPACE, "the forward's work list needs %zu bytes of scratch; the fixed scratch holds %zu",
                 need, kScratchBytes);

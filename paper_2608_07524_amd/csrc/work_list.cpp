@@ -58,7 +58,7 @@ size_t tiles_per_head(const dcp_attn_desc* d, int tile) {
 }
 
 
-UnitList build_units(const dcp_attn_desc* d, int tile, int window_tile, bool keys_major) {
+UnitList build_units(const dcp_attn_desc* d, int tile, int window_tile, bool keys_major, bool heads_together) {
   const int32_t* cu = d->cu_seqlens_host;
   const int32_t H = d->n_heads;
   const int32_t n = d->n_seqs;
@@ -126,8 +126,11 @@ UnitList build_units(const dcp_attn_desc* d, int tile, int window_tile, bool key
   // A window's heads read and write interleaved pieces of the same rows (144
   // bytes each at head width 72, not whole cache lines), so neighbouring heads
   // go to one die as far as every CU of every die still gets two workgroups.
+  // (Without heads_together every head goes to the least-loaded die: lists of
+  // nearly equal length, with the least padding.)
   const int64_t n_win = int64_t(out.window_starts.size() / kWindowWords);
-  const int32_t win_heads = int32_t(std::max<int64_t>(1, std::min<int64_t>(H, n_win * H / (2 * kNumCU))));
+  const int32_t win_heads =
+      heads_together ? int32_t(std::max<int64_t>(1, std::min<int64_t>(H, n_win * H / (2 * kNumCU)))) : 1;
   for (int windows = 0; windows < 2; ++windows) {
     std::vector<std::vector<WorkUnit>> lists(kNumXcd);
     for (auto& l : lists) l.reserve(total / kNumXcd + size_t(cap) + 1);
@@ -194,12 +197,12 @@ size_t window_bytes(const dcp_attn_desc* d, int tile) {
   return align_up(sizeof(uint64_t) * kWindowWords * std::max<size_t>(1, tiles_per_head(d, tile)));
 }
 
-UnitList build_pass(const dcp_attn_desc* d, int32_t pass) {
+UnitList build_pass(const dcp_attn_desc* d, int32_t pass, bool heads_together) {
   const int D = d->head_dim;
   switch (pass) {
-    case kPassFwd: return build_units(d, fwd_tile_rows(D), fwd_window_rows(D), false);
-    case kPassDkdv: return build_units(d, bwd_key_tile_rows(D), bwd_key_window_rows(D), true);
-    default: return build_units(d, bwd_query_tile_rows(D), bwd_query_window_rows(D), false);
+    case kPassFwd: return build_units(d, fwd_tile_rows(D), fwd_window_rows(D), false, heads_together);
+    case kPassDkdv: return build_units(d, bwd_key_tile_rows(D), bwd_key_window_rows(D), true, heads_together);
+    default: return build_units(d, bwd_query_tile_rows(D), bwd_query_window_rows(D), false, heads_together);
   }
 }
 

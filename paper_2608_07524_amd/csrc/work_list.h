@@ -30,8 +30,10 @@ struct UnitList {
 
 // The kernel passes and their lists.
 enum : int32_t { kPassFwd = 0, kPassDkdv = 1, kPassDq = 2 };
-UnitList build_units(const dcp_attn_desc* d, int tile, int window_tile, bool keys_major);
-UnitList build_pass(const dcp_attn_desc* d, int32_t pass);
+// heads_together: neighbouring heads of a packed window on one die (faster;
+// without it the lists are padded least).
+UnitList build_units(const dcp_attn_desc* d, int tile, int window_tile, bool keys_major, bool heads_together);
+UnitList build_pass(const dcp_attn_desc* d, int32_t pass, bool heads_together = true);
 
 // Bytes reserved for one pass's list and for its window masks (upper
 // bounds, padding included, for workspaces sized before the list exists).

@@ -217,3 +217,20 @@ def test_noalloc_forward_rejects_oversize_lists_on_the_host():
     assert lib.dcp_varlen_attn_fwd_noalloc(C.byref(d), 16, 16, 16, 16, 16, None) == N.DCP_ERR_INVALID
     d, keep = _desc([0, 5], 5)
     assert lib.dcp_varlen_attn_fwd_noalloc(C.byref(d), None, 16, 16, 16, 16, None) == N.DCP_ERR_INVALID
+
+
+def test_noalloc_forward_accepts_lists_up_to_its_scratch():
+    """7,943 windows of 64 heads need 508,352 units and 7,943 masks of 32 bytes,
+    8,388,096 bytes with the constants: within the scratch, though not when a
+    window's heads are kept on one die (993 windows on the longest of the eight
+    lists).  One window more does not fit either way.  (Made-up pointers: where
+    there is a device, the accepted call would launch.)"""
+    torch = pytest.importorskip("torch")
+    if torch.cuda.is_available():
+        pytest.skip("without a device only")
+    lib = P.load()
+    for n, fits in ((7943, True), (7944, False)):
+        cu = np.arange(2 * n + 1, dtype=np.int64) * 60
+        d, keep = _desc(cu, int(cu[-1]), H=64, D=64)
+        st = lib.dcp_varlen_attn_fwd_noalloc(C.byref(d), 16, 16, 16, 16, 16, None)
+        assert (st == N.DCP_ERR_WORKSPACE) == (not fits), N.last_error()
