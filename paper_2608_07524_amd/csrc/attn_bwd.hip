@@ -1255,7 +1255,7 @@ hipError_t launch_dq_list(const BwdArgs& a, const WorkUnit* units, int n_units) 
 
 template <int D, bool CAUSAL>
 hipError_t launch_dkdv_tiles(const BwdArgs& a, const WorkUnit* units) {
-  switch (tile_parts(a.n_units, CAUSAL)) {
+  switch (tile_parts(a.n_units, CAUSAL, a.longest, true)) {
     case 8: return launch_dkdv_list<D, CAUSAL, false, false, 4, 4>(a, units, a.n_units);
     case 4: return launch_dkdv_list<D, CAUSAL, false, false, 8, 4>(a, units, a.n_units);
     case 2: return launch_dkdv_list<D, CAUSAL, false, false, 8, 2>(a, units, a.n_units);
@@ -1267,7 +1267,7 @@ template <int D, bool CAUSAL, bool DELTA>
 hipError_t launch_dq_tiles(const BwdArgs& a, const WorkUnit* units) {
   constexpr int W = kBwdDqWaves;
   constexpr int NS = D > 96 ? kBwdDqStagesD128 : kBwdDqStages;  // (also two or three tiles of 128 keys when split)
-  switch (tile_parts(a.n_qunits, CAUSAL)) {
+  switch (tile_parts(a.n_qunits, CAUSAL, a.qlongest, true)) {
     // (8 parts gain nothing over 4 here: 4,096 tokens 213 and 215 us per backward)
     case 8:
     case 4: return launch_dq_list<D, W, NS, CAUSAL, false, DELTA, 4, 1>(a, units, a.n_qunits);

@@ -770,7 +770,7 @@ hipError_t launch_fwd_t(const FwdArgs& a) {
   if (ev.begin) (void)hipEventRecord(ev.begin, a.stream);
   hipError_t e = hipSuccess;
   if (a.n_units > 0) {
-    switch (tile_parts(a.n_units, CAUSAL)) {
+    switch (tile_parts(a.n_units, CAUSAL, a.longest, false)) {
       case 8: e = launch_fwd_list<D, NW / 2, CAUSAL, false, kFwdSplitStages, 4>(a, units, a.n_units); break;
       case 4: e = launch_fwd_list<D, NW, CAUSAL, false, kFwdSplitStages, 4>(a, units, a.n_units); break;
       case 2: e = launch_fwd_list<D, NW, CAUSAL, false, kFwdSplitStages, 2>(a, units, a.n_units); break;

@@ -20,6 +20,7 @@ struct FwdArgs {
   const void* window_starts;  // device: 4 uint64 per packed window
   int n_units;
   int n_wunits;
+  int longest;  // longest sequence with tiles of its own
   int n_heads;
   int head_dim;
   int total_tokens;
@@ -45,10 +46,12 @@ struct BwdArgs {
   const void* window_starts;   // device: 4 uint64 per packed window of the key-tile list
   int n_units;
   int n_wunits;
+  int longest;            // longest sequence with tiles of its own
   const void* qunits;     // device WorkUnit[n_qunits + n_wqunits], query tiles then packed windows
   const void* qwindow_starts;  // device: the same for the query-tile list
   int n_qunits;
   int n_wqunits;
+  int qlongest;           // the same for the query-tile list
   int rows_end;           // cu_seqlens[n]: rows past it are not touched
   int n_heads;
   int head_dim;

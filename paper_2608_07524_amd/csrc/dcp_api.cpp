@@ -175,7 +175,7 @@ int check_bwd_tensors(const void* dout, const void* o, const float* lse, const v
 int run_fwd(const dcp_attn_desc* d, const UnitList& fwd, const void* q, const void* k, const void* v, void* o,
             float* lse, char* ws, size_t units_at, size_t windows_at, hipStream_t s) {
   FwdArgs a{q, k, v, o, lse, ws, ws + units_at, ws + windows_at, int(fwd.n_tiles),
-            int(fwd.units.size() - fwd.n_tiles), d->n_heads, d->head_dim, int(d->total_tokens),
+            int(fwd.units.size() - fwd.n_tiles), fwd.longest, d->n_heads, d->head_dim, int(d->total_tokens),
             d->scale, d->causal, s};
   hipError_t e = launch_fwd(a);
   if (e != hipSuccess) return fail(DCP_ERR_HIP, "forward launch: %s", hipGetErrorString(e));
@@ -188,8 +188,8 @@ int run_bwd(const dcp_attn_desc* d, const UnitList& kl, const UnitList& ql, cons
             size_t delta_at, hipStream_t s) {
   BwdArgs a{dout, o, lse, q, k, v, dq, dk, dv, reinterpret_cast<float*>(ws + delta_at),
             reinterpret_cast<float*>(ws + lse2_at), ws, ws + units_at, ws + windows_at, int(kl.n_tiles),
-            int(kl.units.size() - kl.n_tiles), ws + qunits_at, ws + qwindows_at, int(ql.n_tiles),
-            int(ql.units.size() - ql.n_tiles), d->cu_seqlens_host[d->n_seqs], d->n_heads, d->head_dim,
+            int(kl.units.size() - kl.n_tiles), kl.longest, ws + qunits_at, ws + qwindows_at, int(ql.n_tiles),
+            int(ql.units.size() - ql.n_tiles), ql.longest, d->cu_seqlens_host[d->n_seqs], d->n_heads, d->head_dim,
             int(d->total_tokens), d->scale, d->causal, s};
   hipError_t e = launch_bwd(a);
   if (e != hipSuccess) return fail(DCP_ERR_HIP, "backward launch: %s", hipGetErrorString(e));

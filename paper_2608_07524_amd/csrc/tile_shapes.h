@@ -29,20 +29,42 @@ constexpr int kNumXcd = 8;  // MI355X: 8 accelerator dies, each with its own L2
 constexpr int kNumCU = 256;  // and 32 compute units per die
 
 // How many workgroups share one unit of a sequence-tile list of n_units
-// (padding included): 8 / parts of its rows each, the 8 (or, for 8 parts, 4)
-// wavefronts then splitting the other side of the score matrix as well, so a
-// workgroup's walk is `parts` times shorter.  A workgroup takes most of a
-// CU's LDS, so the chip runs one per CU: parts pay as long as they find idle
-// CUs, and cost where they do not (a barrier per shorter step, and every part
-// streams the same rows).  Forward, 2 heads of width 128, 1 / 2 / 4 / 8 parts:
-// 1,000 tokens (32 units) 32 / 21 / 16 / 15 us; 8,192 (64) 197 / 120 / 92 /
-// 167; 16,384 (128) 399 / 270 / 348 / 636; 20,000 (158) 499 / 580.  Causal
-// units hold half the work on average and come longest first, so two rounds
-// of workgroups still fill the chip: 5,003 tokens (40 units) 121 / 75 / 54 /
-// 53; 20,000 (158) 476 / 285 / 288; 32 heads of 3,001 (384) 108 / 110.
-constexpr int tile_parts(int n_units, bool causal) {
-  const int room = causal ? 2 * kNumCU : kNumCU;
-  return n_units <= room / 8 ? 8 : n_units <= room / 4 ? 4 : n_units <= room / 2 ? 2 : 1;
+// (padding included) whose longest sequence has `longest` rows: 8 / parts of
+// its rows each, the 8 (or, for 8 parts, 4) wavefronts then splitting the other
+// side of the score matrix as well, so a workgroup's walk is `parts` (at 8: 4)
+// times shorter.  A workgroup takes most of a CU's LDS, so the chip runs one per
+// CU: parts pay as long as they find idle CUs, and cost where they do not (a
+// barrier per shorter step, and every part streams the same rows).  Forward, 2
+// heads of width 128, 1 / 2 / 4 / 8 parts: 1,000 tokens (32 units) 32 / 21 / 16 /
+// 15 us; 8,192 (64) 197 / 120 / 92 / 167; 16,384 (128) 399 / 270 / 348 / 636;
+// 20,000 (158) 499 / 580.
+// Causal units hold half the work on average and come longest first, so up to
+// two rounds of workgroups still fill the chip, if the walks are long: 5,003
+// tokens (40 units) 121 / 75 / 54 / 53; 20,000 (158) 476 / 285 / 288.  Short ones
+// are mostly a workgroup's start and end, and a second round doubles that.  Two
+// rounds against one, forward, 48 to 256 units of one length, widths 64 to 128:
+// 300 to 700 tokens 1.02-1.6 x the time, 1,000 1.05-1.3, 1,500 0.68-0.98 with the
+// second round at most half full and 0.97-1.17 fuller, 2,000 0.78 and 0.91-1.13,
+// 3,000 0.77-0.96, 5,000 and more 0.65-1.02; dK/dV and dQ alike.
+// A walk of one or two key tiles is not worth a cut: at most 64 tokens, any parts
+// 1.1-1.4 x the forward and 1.1-1.3 x the backward, 80 to 127 tokens 8 parts
+// 0.78-1.03 and 0.93-1.04, 4 or 2 parts 0.90-1.18 and 0.96-1.18.  From 129 tokens
+// on 8 and 4 parts always pay (forward 0.73-0.86, backward with both passes cut
+// 0.82-0.98); 2 parts in the forward (0.79-1.00), in the backward from about 200
+// (dK/dV and dQ: 129 tokens 1.02-1.06 and 0.94-1.16, 180 0.97-1.02 and 0.92-1.10,
+// 200 0.95-1.01 and 0.85-1.03, 256 0.93-0.98 and 0.91-0.95).
+constexpr int parts_within(int n_units, int workgroups) {
+  return n_units <= workgroups / 8 ? 8 : n_units <= workgroups / 4 ? 4 : n_units <= workgroups / 2 ? 2 : 1;
+}
+constexpr int tile_parts(int n_units, bool causal, int longest, bool backward) {
+  int parts = parts_within(n_units, kNumCU);
+  if (causal && longest >= 1408) {
+    const int more = parts_within(n_units, 2 * kNumCU);
+    if (longest >= 2560 || n_units * more <= kNumCU + kNumCU / 2) parts = more;
+  }
+  if (longest <= 128 && (backward || parts < 8 || longest <= 64)) parts = 1;
+  if (backward && parts == 2 && longest < 192) parts = 1;
+  return parts;
 }
 
 // Offsets (bf16 elements) of the 16-byte constant chunks every attention

@@ -82,6 +82,7 @@ UnitList build_units(const dcp_attn_desc* d, int tile, int window_tile, bool key
   auto add_sequence = [&](int32_t b) {
     const int32_t len = cu[b + 1] - cu[b];
     const int32_t nt = (len + tile - 1) / tile;
+    out.longest = std::max(out.longest, len);
     for (int32_t c0 = 0; c0 < nt; c0 += int32_t(cap)) {
       Group g{0, b, c0, std::min<int32_t>(nt, c0 + int32_t(cap)), -1};
       for (int32_t t = g.t_begin; t < g.t_end; ++t) g.work += tile_work(len, t * tile, std::min(tile, len - t * tile));

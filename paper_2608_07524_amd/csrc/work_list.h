@@ -25,6 +25,7 @@ int check_tensor(const void* p, const char* name);
 struct UnitList {
   std::vector<WorkUnit> units;  // n_tiles sequence tiles, then the packed windows (8 per-die lists each)
   size_t n_tiles = 0;
+  int32_t longest = 0;  // longest sequence with tiles of its own
   std::vector<uint64_t> window_starts;  // kWindowWords per packed window
 };
 

@@ -151,14 +151,23 @@ def test_running_max_moves(torch, D, causal, regime):
 
 # Batches of few tiles: each tile is shared by 8, 4 or 2 workgroups whose
 # wavefronts split the keys (forward, dQ) or queries (dK/dV) into streams.  The
-# head count moves a batch across the rule (256 units for one part each, twice
-# that when causal); lengths leave whole parts, a stream's first or last blocks,
-# or all but one row of the last part empty.
+# head count moves a batch across the rule (256 units for one part each); lengths
+# leave whole parts, a stream's first or last blocks, or all but one row of the
+# last part empty.
 @pytest.mark.parametrize("D", [64, 72, 128])
 @pytest.mark.parametrize("H,causal,lengths", [
     (1, False, [129]), (1, True, [257]), (2, False, [1025, 130, 300]), (2, True, [1025, 130, 300]),  # 8 parts
-    (9, False, [225, 993, 256]), (16, True, [225, 993, 480]),                                        # 4
-    (17, False, [385, 250, 545]), (33, True, [385, 250, 545])])                                      # 2
+    (9, False, [225, 993, 256]),                                                                     # 4
+    (16, True, [225, 993, 480]), (17, False, [385, 250, 545]),                                       # 2
+    (33, True, [385, 250, 545]),                                                                     # 1
+    # causal batches take twice the units from a longest sequence of 2,560 tokens on, half
+    # as many more from 1,408 ...
+    (4, True, [2560]), (17, True, [2600]), (17, True, [2559]), (40, True, [2600, 130]),
+    (24, True, [1408, 130]), (24, True, [1407, 130]),
+    # ... and short walks are not cut (at all up to 64 rows, but in 8 for the forward up to 128,
+    # not in 2 for the backward below 192)
+    (2, False, [64]), (2, True, [65]), (9, False, [128]), (9, True, [129] * 4), (16, True, [191] * 5),
+    (16, False, [192, 130] * 3)])
 def test_tile_parts(torch, D, H, causal, lengths):
     got, ref, n = _run_case(torch, lengths, H, D, causal, seed=D + H)
     _assert_close(got, ref, n, f"parts H={H} D={D} causal={causal}")

@@ -3,10 +3,15 @@ exactly once, tiles never straddle two sequences, and packed windows hold
 whole runs of consecutive short sequences whose start masks decode to the
 true sequence bounds of every row."""
 
+import os
+import shutil
+import subprocess
+
 import numpy as np
 import pytest
 
 from paper_2608_07524_amd import _native as N
+from paper_2608_07524_amd import build as B
 from paper_2608_07524_amd import inputs as I
 
 
@@ -137,3 +142,28 @@ def test_computed_pairs_accounting():
     mw = B.matrix_work(P, w)
     assert mw["fwd_fill"] == 5050 / 10240 and mw["dkdv_fill"] == 5050 / 10240
     assert mw["executed_flop_per_step"] == 2.0 * (2 + 4 + 3) * 10240 * 64
+
+
+def test_parts_of_a_tile(tmp_path):
+    """How many workgroups share a tile: never more than fill the chip once
+    (256), except over causal batches with long sequences; nothing is cut in
+    the backward where every sequence is one or two key tiles."""
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ is not installed")
+    src, exe = tmp_path / "parts.cpp", str(tmp_path / "parts")
+    src.write_text('#include "tile_shapes.h"\n#include <cstdio>\nint main() { int n, c, l, b;\n'
+                   'while (scanf("%d%d%d%d", &n, &c, &l, &b) == 4) printf("%d\\n", dcp::tile_parts(n, c, l, b)); }\n')
+    subprocess.run([gxx, "-std=c++17", "-I", B.CSRC, str(src), "-o", exe], check=True)
+    lengths = (1, 64, 65, 128, 129, 191, 192, 300, 1407, 1408, 2559, 2560, 20000)
+    asked = [(n, c, l, b) for n in range(8, 1100, 8) for c in (0, 1) for l in lengths for b in (0, 1)]
+    out = subprocess.run([exe], input="".join("%d %d %d %d\n" % a for a in asked), capture_output=True, text=True,
+                         check=True).stdout.split()
+    for (n, c, l, b), parts in zip(asked, map(int, out)):
+        assert parts in (1, 2, 4, 8)
+        limit = 512 if c and l >= 2560 else 384 if c and l >= 1408 else 256
+        assert parts == 1 or n * parts <= limit, (n, c, l, b, parts)
+        if l <= 64 or (b and l <= 128):
+            assert parts == 1, (n, c, l, b, parts)
+    # eight documents of 300 tokens, 8 heads, causal: one round, as without the mask
+    assert out[asked.index((128, 1, 300, 0))] == out[asked.index((128, 0, 300, 0))] == "2"
