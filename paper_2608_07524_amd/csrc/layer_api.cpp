@@ -182,32 +182,57 @@ int gemm(rocblas_handle hd, bool ta, bool tb, int64_t M, int64_t N, int64_t K, c
 }
 
 // Which projections layer_proj.hip takes.  It saves launches and passes over
-// memory; the library's main loop is faster once the contraction is long.  Library /
-// fused, us, at (hidden, tokens):
+// memory; the library's main loop is faster once the contraction is long, and
+// where its 256-wide tiles fit the hidden size and 192-wide ones do not.
+// Library / fused, us, at (hidden, tokens):
 //   Q, K, V    (1152, 300) 28 / 15, (1152, 16381) 175 / 145, (2048, 1000) 61 /
 //              39, (2048, 4000) 111 / 126, (3072, 1000) 89 / 66, (3072, 8192) 406 / 425
 //   W_up+GELU  (1152, 300) 16 / 17, (1152, 1000) 31 / 22, (1152, 16381) 237 /
 //              201, (2048, 1000) 48 / 51, (2048, 16000) 521 / 543
 //   W_down^T+GELU'  (1152, 300) 14 / 18, (1152, 1000) 27 / 23, (1152, 16381)
 //              249 / 221, (2048, 1000) 47 / 50, (2048, 16000) 522 / 563
-//   W_o, W_down with their residuals and dO: inside a step (cold operands) the
-//              library's products take 89, 225 and 68 us at (1152, 16381), not the
-//              59, 160 and 47 they take repeated, these stay within 5 %.  Whole
-//              step: (1152, 2500) 550 / 553, (1152, 4100) 746 / 757, (1152, 8192)
-//              1,258 / 1,227, (1440, 8192) 1,879 / 1,844, (1152, 16381) 2,397 /
-//              2,323; just past one round of tiles (512) the second is too empty,
-//              (1440, 10240; 640 tiles) 2,378 / 2,400
 //   dY1        (1152, 1000) 29 / 39, (1152, 2500) 43 / 42, (1152, 16381) 185 /
 //              137, (2048, 4000) 127 / 135
+// Hidden sizes between, inside a step, fused less library at 4,096 / 8,192 /
+// 16,384 / 24,576 tokens:
+//   Q, K, V    1,024 -4 / -4 / +18 / +24; 1,280 -24 / -28 / -37 / +14; 1,536 -18 /
+//              -8 / -17 / -6; 1,664 -21 / -34 / -17 / -41; 1,792 -17 / +7 / +31 / +42
+//   W_up+GELU  1,024 -1 / -7 / +5 / +13; 1,280 -20 / -17 / -16 / -23; 1,536 -16 /
+//              -1 / -7 / -5; 1,664 -5 / -3 / -1 / +1; 1,792 -3 / -14 / +5 / -33
+//   W_down^T+GELU'  1,024 +5 / +3 / +7 / +18; 1,280 -8 / -28 / +18 / +45; 1,536 -3 /
+//              +6 / +8 / +15; 1,664 +5 / 0 / +6 / +37; 1,792 +3 / -12 / +60 / -19
+//   dY1        1,024 -6 / -13 / -8 / -20; 1,536 -6 / -13 / -30 / -48; 1,792 +3 / -2 /
+//              +18 / -41
 constexpr int64_t kProjHidden = 1536;
-constexpr int64_t kPlainTokens = 6144;
-inline bool fused_qkv(const Dims& d) { return d.h <= kProjHidden || d.T * d.h <= int64_t(4) << 20; }
-inline bool fused_gelu(const Dims& d) { return d.h <= kProjHidden && d.T >= 512; }
-inline bool fused_plain(const Dims& d) {
-  const int64_t tiles = (d.T + 127) / 128 * ((d.h + 191) / 192);
-  return d.h <= kProjHidden && d.T >= kPlainTokens && (tiles <= 512 || tiles >= 768);
+constexpr int64_t kProjTile = 192;
+inline int64_t proj_tiles(int64_t n) { return (n + kProjTile - 1) / kProjTile; }
+// (1,024 and smaller powers of two: 192-wide tiles pad them by an eighth or more)
+inline bool library_width(const Dims& d) {
+  return d.h % 256 == 0 && 10 * kProjTile * proj_tiles(d.h) > 11 * d.h && d.T * d.h > int64_t(12) << 20;
 }
+inline bool fused_qkv(const Dims& d) {
+  return (d.h <= kProjHidden && !library_width(d)) || d.T * d.h <= int64_t(4) << 20;
+}
+inline bool fused_gelu(const Dims& d) { return d.h <= kProjHidden && d.T >= 512 && !library_width(d); }
 inline bool fused_dy1(const Dims& d) { return d.h <= kProjHidden && d.T >= 2048; }
+// W_o with its residual and dO (contraction h), W_down with its residual (4 h),
+// from 6,144 tokens; below, the library is a little faster.  Where the host's
+// enqueueing bounds the step (hidden 256, 6,144 tokens: 73 us forward) all three
+// save a library call's 10 to 13 us of it.  Otherwise W_o and dO, if the library's
+// 256-wide tiles do not divide the hidden size and the last round of 512 workgroups
+// (two per CU) is mostly full.  Fused less library, change of the forward by W_o and
+// of the step by dO: 108 sizes within the rule (768 to 1,472 wide, 6,144 to 28,672
+// tokens) -1.2 % (worst +2.3, best -5) and -0.3 %; hidden 1,152: 336 tiles (0.66 of
+// a round) +7.9 us of 310, 384 (0.75) -4.7 of 385, 768 -16.5 of 710, 1,152 -17 of
+// 1,020; multiples of 256: 1,024 +4 to +26, 1,536 -18 to +20.  W_down is the
+// library's: +10 to +60 us at most sizes (1,152 wide: 10,240 tokens +5, 12,288 +34,
+// 24,576 +10; 1,440: +11 to +62), -25 only around 768 tiles of hidden 1,152.
+constexpr int64_t kPlainTokens = 6144;
+inline bool enqueue_bound(const Dims& d) { return d.T >= kPlainTokens && d.T * d.h <= int64_t(2) << 20; }
+inline bool fused_square(const Dims& d) {
+  const int64_t tiles = (d.T + 127) / 128 * proj_tiles(d.h), rounds = (tiles + 511) / 512;
+  return enqueue_bound(d) || (d.h <= kProjHidden && d.h % 256 != 0 && d.T >= kPlainTokens && 10 * tiles >= 7 * 512 * rounds);
+}
 
 int check_ptrs(std::initializer_list<const void*> ps, const char* what) {
   for (const void* p : ps)
@@ -246,13 +271,13 @@ int forward(const dcp_layer_desc* L, const Dims& d, const dcp_layer_weights* w, 
   DCP_TRY(dcp_varlen_attn_fwd(L->attn, at(sb, s.q), at(sb, s.k), at(sb, s.v), at(sb, s.o),
                               reinterpret_cast<float*>(at(sb, s.lse)), attn_ws, attn_ws_bytes, st));
   // A W + residual; hidden-wide output
-  auto add = [&](const void* a, const void* wt, const void* res, void* dst, int64_t K) -> int {
-    if (!fused_plain(d)) return gemm(hd, false, false, T, h, K, a, wt, 1.f, res, dst, false);
+  auto add = [&](bool fused, const void* a, const void* wt, const void* res, void* dst, int64_t K) -> int {
+    if (!fused) return gemm(hd, false, false, T, h, K, a, wt, 1.f, res, dst, false);
     const Proj p{{a}, {wt}, {dst}, res, nullptr, T, int(h), int(K), 1, 1, 0};
     DCP_HIP(launch_proj(p, ProjEpilogue::kResidual, st));
     return DCP_OK;
   };
-  DCP_TRY(add(at(sb, s.o), w->wo, x, at(sb, s.hres), h));
+  DCP_TRY(add(fused_square(d), at(sb, s.o), w->wo, x, at(sb, s.hres), h));
   DCP_HIP(launch_rmsnorm_fwd(at(sb, s.hres), w->norm2, at(sb, s.y2), reinterpret_cast<float*>(at(sb, s.rstd2)), T,
                              int(h), L->eps, st));
   if (fused_gelu(d)) {
@@ -262,7 +287,7 @@ int forward(const dcp_layer_desc* L, const Dims& d, const dcp_layer_weights* w, 
     DCP_TRY(gemm(hd, false, false, T, 4 * h, h, at(sb, s.y2), w->w_up, 0.f, at(sb, s.u), at(sb, s.u), false));
     DCP_HIP(launch_gelu_fwd(at(sb, s.u), at(sb, s.a), T * 4 * h, st));
   }
-  DCP_TRY(add(at(sb, s.a), w->w_down, at(sb, s.hres), out, 4 * h));
+  DCP_TRY(add(enqueue_bound(d), at(sb, s.a), w->w_down, at(sb, s.hres), out, 4 * h));
   return DCP_OK;
 }
 
@@ -355,7 +380,7 @@ extern "C" int dcp_layer_bwd(const dcp_layer_desc* L, const dcp_layer_weights* w
                              int(h), st));
   // attention block: dO = dH Wo^T; attention backward
   void* dO = at(workspace, b.dy1);  // dY1 is not needed yet: its space holds dO (bf16) first
-  if (fused_plain(d)) {
+  if (fused_square(d)) {
     const Proj p{{at(workspace, b.dh)}, {w->wo}, {dO}, nullptr, nullptr, T, int(h), int(h), 1, 1, 0};
     DCP_HIP(launch_proj(p, ProjEpilogue::kStoreT, st));
   } else {

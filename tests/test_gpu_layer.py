@@ -133,11 +133,12 @@ def test_shared_gradient_buffer(torch, H, D, lengths):
 # The projections' tiles are 192 features x 64 or (more than 256 tiles) 128
 # tokens, their slices 64 of the contraction.  Widths of one slice, of a slice
 # and a remainder, across a feature tile; tokens at and around the counts from
-# which GELU (512), dY1 (2,048) and the rest (6,144) are taken, and at tile edges; both tile
+# which GELU (512), dY1 (2,048) and, for short rows or full rounds of tiles, the
+# others (6,144; 45,990 x 72 is 360 tiles) are taken, and at tile edges; both tile
 # heights of every product.  (The wide ones: every count of 512-column chunks the
 # RMSNorm backward is built for.)
 @pytest.mark.parametrize("H,D,lengths", [(1, 64, [512]), (1, 72, [511, 1]), (3, 72, [513]), (4, 72, [2047, 66]),
-                                         (2, 128, [1025, 1023]), (1, 72, [70] * 476),
+                                         (2, 128, [1025, 1023]), (1, 72, [70] * 476), (1, 72, [70] * 657),
                                          (1, 72, [70] * 88), (16, 72, [300, 277]),
                                          (16, 128, [33]), (20, 128, [17]), (28, 128, [17])])
 def test_projections(torch, H, D, lengths):
