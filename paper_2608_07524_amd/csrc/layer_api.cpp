@@ -234,6 +234,14 @@ inline bool fused_square(const Dims& d) {
   return enqueue_bound(d) || (d.h <= kProjHidden && d.h % 256 != 0 && d.T >= kPlainTokens && 10 * tiles >= 7 * 512 * rounds);
 }
 
+// The weight gradients are the library's at hidden size 4,096, the largest, with
+// many tokens: its tiles divide 4,096, 192-wide ones pad each side by 3 %.  One
+// launch of all six less six products, change of the step: 4,096 at 2,048 / 8,192 /
+// 10,240 / 12,288 / 16,384 / 32,768 tokens -2.0 / +0.1 / -0.9 / +0.6 to +2.3 / +1.4
+// to +2.8 / +3.3 %; 2,048 (as much padding) -4.1 / -4.9 / - / -5.7 / -4.8 / -0.9,
+// 3,840 -4.3 / -6.6 / - / -4.6 / -4.2 / -4.6.
+inline bool library_wgrad(const Dims& d) { return d.h >= 4096 && d.T >= 12288; }
+
 int check_ptrs(std::initializer_list<const void*> ps, const char* what) {
   for (const void* p : ps)
     if (!p || reinterpret_cast<uintptr_t>(p) % 16) return fail(DCP_ERR_INVALID, "%s: null or not 16-byte aligned", what);
@@ -400,7 +408,7 @@ extern "C" int dcp_layer_bwd(const dcp_layer_desc* L, const dcp_layer_weights* w
     DCP_TRY(gemm(hd, false, true, T, h, h, at(workspace, b.dk), w->wk, 1.f, dY1, dY1, true));
     DCP_TRY(gemm(hd, false, true, T, h, h, at(workspace, b.dv), w->wv, 1.f, dY1, dY1, true));
   }
-  // every weight gradient in one launch: dWdown += A^T dout, dWup += Y2^T dU,
+  // the weight gradients, in one launch: dWdown += A^T dout, dWup += Y2^T dU,
   // dWo += O^T dH, dW{q,k,v} += Y1^T d{Q,K,V}
   const int hi = int(h);
   const WgradBatch wb{{{at(sb, s.a), dout, g->w_down, 4 * hi, hi, 0},
@@ -410,7 +418,11 @@ extern "C" int dcp_layer_bwd(const dcp_layer_desc* L, const dcp_layer_weights* w
                        {at(sb, s.y1), at(workspace, b.dk), g->wk, hi, hi, 0},
                        {at(sb, s.y1), at(workspace, b.dv), g->wv, hi, hi, 0}},
                       T, 0, 0};
-  DCP_HIP(launch_wgrad(wb, at(workspace, b.gemm), kGemmWorkspace, st));
+  if (library_wgrad(d)) {
+    for (const WgradProblem& p : wb.p) DCP_TRY(gemm(hd, true, false, p.m, p.n, T, p.a, p.b, 1.f, p.c, p.c, true));
+  } else {
+    DCP_HIP(launch_wgrad(wb, at(workspace, b.gemm), kGemmWorkspace, st));
+  }
   // dX = dH + RMSNorm backward of dY1
   DCP_HIP(launch_rmsnorm_bwd(reinterpret_cast<float*>(dY1), x, w->norm1, reinterpret_cast<float*>(at(sb, s.rstd1)),
                              at(workspace, b.dh), dx, partial, g->norm1, T, int(h), st));

@@ -109,6 +109,31 @@ def test_weight_gradients(torch, H, D, lengths):
     assert max(errs.values()) <= GRAD_TOL, errs
 
 
+# At hidden 4,096 the weight gradients are six library products from 12,288 tokens
+# on: the sum of the gradients of the batch's halves, which are not.
+def test_weight_gradients_of_many_wide_tokens(torch):
+    import paper_2608_07524_amd as P
+    H, D, T = 32, 128, 12288
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    rand = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    W = {n: (rand(*s) / (math.sqrt(s[0]) if len(s) > 1 else 1.0)).to(torch.bfloat16)
+         for n, s in P.layer_param_shapes(H * D).items()}
+    x, dout = (rand(T, H * D).to(torch.bfloat16) for _ in range(2))
+
+    def grads(rows):
+        g = {n: torch.full(w.shape, 3.0, dtype=torch.float32, device="cuda") for n, w in W.items()}
+        for lo in range(0, T, rows):
+            layer = P.Layer(W, g, np.arange(0, rows + 1, 512), H, D, True, None, 1e-6)
+            layer.fwd(x[lo:lo + rows])
+            layer.bwd(x[lo:lo + rows], dout[lo:lo + rows])
+            torch.cuda.synchronize()
+        return g
+
+    whole, halves = grads(T), grads(T // 2)
+    errs = {n: float((whole[n] - halves[n]).abs().max() / (halves[n] - 3.0).abs().max()) for n in W}
+    assert max(errs.values()) <= GRAD_TOL, errs
+
+
 # Matrices that share one gradient buffer: it receives the sum, whether the
 # tokens are split over workgroups (few tiles) or not.
 @pytest.mark.parametrize("H,D,lengths", [(3, 64, [600, 141]), (16, 72, [33, 32])])
