@@ -174,12 +174,19 @@ def test_tile_parts(torch, D, H, causal, lengths):
 
 
 # Batches of more than 512 units take Delta from a pass of its own, smaller ones
-# (every other test here) form it in the passes: many heads of tiles and windows,
+# (most other tests here) form it in the passes: many heads of tiles and windows
+# (causal: the fused dK/dV + dQ windows of the narrow heads read it from memory),
 # and many windows beside tiles few enough to be cut.
 @pytest.mark.parametrize("D", [64, 72, 128])
-@pytest.mark.parametrize("H,causal,lengths", [(64, True, [300, 1, 129, 64, 0, 257, 600, 70, 90]),
+@pytest.mark.parametrize("H,causal,lengths", [(64, True, [300, 1, 129, 64, 0, 257, 600, 70, 90, 40, 50, 30, 100, 27]),
+                                              (64, True, [300, 1, 129, 64, 0, 257, 600, 70, 90]),
                                               (32, False, [300] + [100, 27] * 20)])
 def test_delta_pass(torch, D, H, causal, lengths):
+    from paper_2608_07524_amd import _native as N
+    cu = I.cu_from_lengths(lengths)
+    assert len(N.work_list(cu, H, D, causal, 2)[0]) > 512
+    # (the second list of lengths packs no window of 128 rows)
+    assert len(N.work_list(cu, H, D, causal, 1)[2]) > 0 or len(lengths) == 9
     got, ref, n = _run_case(torch, lengths, H, D, causal, seed=D + H)
     _assert_close(got, ref, n, f"Delta pass H={H} D={D} causal={causal}")
 
