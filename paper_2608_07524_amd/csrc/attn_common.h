@@ -50,18 +50,13 @@ __device__ __forceinline__ void window_bounds(const uint64_t* __restrict__ start
 #define DCP_INLINE __attribute__((always_inline))
 
 
-// The dispatcher hands workgroup i to die i % 8.  Work lists are laid out
-// as 8 consecutive per-die lists of `per_xcd` entries, so a die walks its
-// own list in order and tiles that share K/V (or Q/dO) meet in its L2.
-__device__ __forceinline__ const WorkUnit& unit_for_block(const WorkUnit* units, int per_xcd) {
-  const int i = blockIdx.x;
-  return units[(i % kNumXcd) * per_xcd + i / kNumXcd];
-}
-
-// As unit_for_block when each unit is shared by PARTS workgroups of `rows`
-// rows each: they follow one another on the unit's die.  `reverse` hands the
-// last rows out first (causal query tiles: the part with the most keys).
-// rows == 0 in the result: nothing to do.
+// This workgroup's unit.  The dispatcher hands workgroup i to die i % 8.  Work
+// lists are laid out as 8 consecutive per-die lists of `per_xcd` entries, so a
+// die walks its own list in order and tiles that share K/V (or Q/dO) meet in its
+// L2.  Each unit is shared by PARTS workgroups of `rows` rows: they follow one
+// another on the unit's die.  `reverse` hands the last rows out first (causal
+// query tiles: the part with the most keys).  rows == 0 in the result: nothing
+// to do.
 template <int PARTS>
 __device__ __forceinline__ WorkUnit part_for_block(const WorkUnit* units, int per_xcd, int rows, bool reverse) {
   const int i = blockIdx.x, pos = i / kNumXcd;

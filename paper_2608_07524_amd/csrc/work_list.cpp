@@ -39,7 +39,7 @@ int check_tensor(const void* p, const char* name) {
 }
 
 // Tiles of `tile` rows per (sequence, head), never straddling two
-// sequences, laid out as 8 per-die lists (see unit_for_block).  Runs of
+// sequences, laid out as 8 per-die lists (see part_for_block).  Runs of
 // consecutive sequences shorter than `window_tile` (<= tile) share one
 // tile as a packed window of at most `window_tile` rows (each row still
 // attends only within its own sequence), so thousands of short sequences do
