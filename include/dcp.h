@@ -126,7 +126,10 @@ int dcp_varlen_attn_fwd(const dcp_attn_desc* desc, const void* q, const void* k,
  *                 query-stationary workgroups (or, for packed windows at head
  *                 widths up to 96, by the window's dK/dV workgroup), so every
  *                 gradient is written once and is bitwise reproducible.
- * The call uses the same desc (scale, causal) as the forward.  Outputs do not
+ * The call uses the same desc (scale, causal) as the forward.  Results are
+ * bitwise reproducible for a batch; a sequence's last bits can depend on how many
+ * tiles the whole batch has (forward and backward: the number of workgroups that
+ * share a tile, and here the way rowsum(dO o O) is formed).  Outputs do not
  * overlap inputs or each other, except that dq may be q's or dout's buffer and
  * one of the three o's (a small batch then takes one launch more).
  */

@@ -1,8 +1,9 @@
-"""GPU properties: run-to-run bitwise determinism of every output, bitwise
-invariance of a sequence's outputs to its position in the pack (sequences
-that run in tiles of their own), the same within the parity bounds for
-short sequences sharing a packed window, and the cost profiler feeding the
-planner."""
+"""GPU properties: run-to-run bitwise determinism of every output; bitwise
+invariance of a sequence's outputs to its position in the pack and to its
+neighbours (sequences that run in tiles of their own, while the batch keeps its
+parts per tile and its way to Delta), the same within the parity bounds where
+the batch's size changes those, or where short sequences share a packed window;
+and the cost profiler feeding the planner."""
 
 import math
 
@@ -146,7 +147,8 @@ def test_outputs_in_input_storage(torch, D, H, causal, lengths, dq_in, dk_in):
 @pytest.mark.parametrize("causal", [False, True])
 def test_position_in_pack_invariance(torch, causal):
     """A sequence's outputs do not depend on where it sits in the pack or
-    on its neighbours (no cross-sequence reads)."""
+    on its neighbours (no cross-sequence reads).  (Both batches are cut into
+    eight parts per tile and form Delta in the passes.)"""
     rng = np.random.default_rng(8)
     H, D = 2, 72
     target = I.tensors(rng, 333, H, D)
@@ -161,6 +163,47 @@ def test_position_in_pack_invariance(torch, causal):
             assert np.array_equal(x, y[:, sl])
         else:
             assert np.array_equal(x, y[sl])
+
+
+def _close(a, b):
+    """Two results of one computation, each within the parity bounds of the
+    exact one (bf16 store rounding of O added)."""
+    from gpu_util import BF16_U, GRAD_TOL, LSE_TOL, O_TOL
+    x = [I.bf16_to_f64(t) for t in (a[0], b[0])]
+    assert np.max(np.abs(x[0] - x[1]) - 2 * BF16_U * np.abs(x[0])) <= 2 * O_TOL
+    assert np.max(np.abs(a[1] - b[1])) <= LSE_TOL
+    for g, h in zip(a[2:], b[2:]):
+        g, h = I.bf16_to_f64(g), I.bf16_to_f64(h)
+        assert np.max(np.abs(g - h)) <= GRAD_TOL * np.max(np.abs(g))
+
+
+# 333 + n x 300 tokens of 2 heads (4 + 4 n units, padded): cut in 8 parts alone, then in 4,
+# 2 and 1, the last with more than the 512 units whose Delta the passes form.
+@pytest.mark.parametrize("D", [72, 128])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("n,units", [(9, 48), (20, 96), (40, 176), (140, 576)])
+def test_neighbours_that_change_the_parts(torch, D, causal, n, units):
+    """Where neighbours move the batch across a threshold, a sequence's sums
+    are grouped otherwise: the same outputs within the parity bounds, and, the
+    batch's lengths being the same, the same bits at another place in it."""
+    from paper_2608_07524_amd import _native as N
+    rng = np.random.default_rng(10)
+    H = 2
+    target, rest = I.tensors(rng, 333, H, D), I.tensors(rng, 300 * n, H, D)
+    solo = _outputs(torch, target, [0, 333], 0.1, causal)
+
+    def packed(before):
+        cu = I.cu_from_lengths([300] * before + [333] + [300] * (n - before))
+        assert len(N.work_list(cu, H, D, causal, 0)[0]) == units
+        cut = 300 * before
+        bits = [np.concatenate([r[:cut], t, r[cut:]]) for t, r in zip(target, rest)]
+        out = _outputs(torch, bits, cu, 0.1, causal)
+        return [o[:, cut:cut + 333] if i == 1 else o[cut:cut + 333] for i, o in enumerate(out)]
+
+    first, last = packed(0), packed(n)
+    _close(solo, first)
+    for x, y in zip(first, last):
+        assert np.array_equal(x, y)
 
 
 @pytest.mark.parametrize("causal", [False, True])
