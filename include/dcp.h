@@ -403,12 +403,14 @@ int dcp_plan(const int64_t* seq_lens, int32_t n_seqs, const int32_t* batch_offse
  *   out = h + a Wdown.
  * RMSNorm(z; g) = z * g / sqrt(mean(z^2) + eps) per row.  hidden = H*D of
  * `attn`, at most 4096 (DCP_ERR_UNSUPPORTED beyond); every row of x is a
- * token of some sequence (cu_seqlens[n] must equal total_tokens).  Weight gradients
- * are formed by one HIP kernel, Q, K and V, the MLP's products with GELU and dY1
- * by others at hidden sizes up to 1,536 (Q, K, V also beyond, with few tokens); the
- * other GEMMs run in rocBLAS (bf16 in, fp32 accumulation), with their scratch taken from the caller's workspace; the rocBLAS handle
- * (one per thread and device, kept until the thread ends) is the only
- * device memory the library itself holds.
+ * token of some sequence (cu_seqlens[n] must equal total_tokens).  Products (bf16
+ * in, fp32 accumulation) run in HIP kernels of this library -- all six weight
+ * gradients, but at hidden 4,096 from 12,288 tokens; up to hidden size 1,536 Q, K
+ * and V (beyond it with few tokens), from 512 tokens the MLP's two with GELU, from
+ * 2,048 dY1 and from 6,144, at the sizes where that is faster, W_o and dO -- and
+ * otherwise in rocBLAS, with their scratch taken from the caller's workspace; the
+ * rocBLAS handle (one per thread and device, kept until the thread ends) is the
+ * only device memory the library itself holds.
  */
 typedef struct {
   const dcp_attn_desc* attn;

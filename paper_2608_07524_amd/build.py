@@ -23,8 +23,8 @@ LIB = os.path.join(PKG, "libdcp.so")
 PROBE_SOURCES = ["probe/dma_copy.hip", "probe/mfma_rate.hip"]
 PROBE_LIB = os.path.join(PKG, "libdcp_probe.so")
 
-SOURCES = ["attn_fwd.hip", "attn_bwd.hip", "layer.hip", "layer_gemm.hip", "layer_proj.hip", "dcp_api.cpp", "dcp_error.cpp", "work_list.cpp",
-           "dcp_plan.cpp", "layer_api.cpp", "noalloc.hip"]
+SOURCES = ["attn_fwd.hip", "attn_bwd.hip", "layer.hip", "layer_gemm.hip", "layer_proj.hip", "dcp_api.cpp",
+           "dcp_error.cpp", "work_list.cpp", "dcp_plan.cpp", "layer_api.cpp", "noalloc.hip"]
 
 # Packed fp32 vector ops stay disabled for device code (plain scalar fp32
 # VALU only); the host pass reports the feature as unknown, which is benign.

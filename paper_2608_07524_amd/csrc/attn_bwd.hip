@@ -1224,7 +1224,9 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_kernel(
 // of a sequence-tile list becomes waves * QS / NW workgroups.
 template <int D, bool CAUSAL, bool PACKED, bool FUSED = false, int NW = 0, int QS = 1, bool DELTA = false>
 hipError_t launch_dkdv_list(const BwdArgs& a, const WorkUnit* units, int n_units) {
-  constexpr DkdvShape sh = QS > 1 ? bwd_dkdv_split_shape(D, NW, QS) : PACKED ? bwd_dkdv_window_shape(D) : bwd_dkdv_shape(D);
+  constexpr DkdvShape sh = QS > 1   ? bwd_dkdv_split_shape(D, NW, QS)
+                           : PACKED ? bwd_dkdv_window_shape(D)
+                                    : bwd_dkdv_shape(D);
   constexpr int PARTS = PACKED ? 1 : bwd_dkdv_shape(D).waves * QS / sh.waves;
   // (QS 4 at head width 128: only the minimal stride leaves room for two tiles)
   constexpr int OSTR = QS == 4 && D > 96 ? BwdShape<D>::DP + 8 : BwdShape<D>::OSTR;
@@ -1244,10 +1246,11 @@ hipError_t launch_dkdv_list(const BwdArgs& a, const WorkUnit* units, int n_units
 template <int D, int NW, int NS, bool CAUSAL, bool PACKED, bool DELTA, int KS = 1, int NKB = 2>
 hipError_t launch_dq_list(const BwdArgs& a, const WorkUnit* units, int n_units) {
   constexpr int PARTS = PACKED ? 1 : kBwdDqWaves * KS / NW;
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, NW, NS, CAUSAL, PACKED, kBwdDqOneCopy, KS, NKB, DELTA>), dim3(n_units * PARTS),
-                     dim3(64 * NW), 0, a.stream, static_cast<const __bf16*>(a.q), static_cast<const __bf16*>(a.k),
-                     static_cast<const __bf16*>(a.v), static_cast<const __bf16*>(a.o),
-                     static_cast<const __bf16*>(a.dout), a.lse, a.lse2, a.ndelta, static_cast<__bf16*>(a.dq), static_cast<const __bf16*>(a.consts), units,
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, NW, NS, CAUSAL, PACKED, kBwdDqOneCopy, KS, NKB, DELTA>),
+                     dim3(n_units * PARTS), dim3(64 * NW), 0, a.stream, static_cast<const __bf16*>(a.q),
+                     static_cast<const __bf16*>(a.k), static_cast<const __bf16*>(a.v), static_cast<const __bf16*>(a.o),
+                     static_cast<const __bf16*>(a.dout), a.lse, a.lse2, a.ndelta, static_cast<__bf16*>(a.dq),
+                     static_cast<const __bf16*>(a.consts), units,
                      static_cast<const uint64_t*>(a.qwindow_starts), n_units / kNumXcd, a.n_heads, a.total_tokens,
                      a.scale, a.scale * kLog2e);
   return hipGetLastError();
@@ -1266,6 +1269,8 @@ hipError_t launch_dkdv_tiles(const BwdArgs& a, const WorkUnit* units) {
 template <int D, bool CAUSAL, bool DELTA>
 hipError_t launch_dq_tiles(const BwdArgs& a, const WorkUnit* units) {
   constexpr int W = kBwdDqWaves;
+  // (at head width 128 the uncut form spills 10-12 registers outside the products, two
+  // streams 44-48; one block per stream and step, as with four, spills none)
   constexpr int NS = D > 96 ? kBwdDqStagesD128 : kBwdDqStages;  // (also two or three tiles of 128 keys when split)
   switch (tile_parts(a.n_qunits, CAUSAL, a.qlongest, true)) {
     // (8 parts gain nothing over 4 here: 4,096 tokens 213 and 215 us per backward)

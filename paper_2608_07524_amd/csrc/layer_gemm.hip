@@ -15,9 +15,9 @@
 // reads.  74 KB of LDS and at most 256 registers: two workgroups share a CU, so
 // one computes while the other waits at its barrier (one workgroup of eight
 // wavefronts with a 192 x 384 tile and a four-stage ring: 8-14 % slower).
-// Bound by the matrix cores at the clock the card holds under them (1.9 GHz;
-// no bank conflicts, slices from L2 or from memory alike within 4 %); at few
-// tokens, by reading and writing C.  Measured, all six gradients, as library
+// Bound by the matrix cores at the clock the card holds under them (counted 1.9
+// GHz at hidden 1,152, 1.7 at 3,072; no bank conflicts, 3 TB/s from memory); at
+// few tokens, by reading and writing C.  Measured, all six gradients, as library
 // GEMMs and here: hidden 1,152, 300 / 4,000 / 16,381 tokens 81 / 324 / 1,185 ->
 // 34 / 143 / 481 us (1,084 TFLOP/s); hidden 3,072, 300 / 2,000 / 8,192 tokens
 // 315 / 737 / 1,994 -> 272 / 536 / 1,541 us (1,204 TFLOP/s).

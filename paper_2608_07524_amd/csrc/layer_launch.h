@@ -1,4 +1,4 @@
-// Host-side launch interface of the layer kernels (layer.hip, layer_gemm.hip).
+// Host-side launch interface of the layer kernels (layer.hip, layer_gemm.hip, layer_proj.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>

@@ -11,10 +11,12 @@
 // contraction (a whole cache line of every row) arrive through a two-stage ring
 // of direct global-to-LDS copies; at TB = 2 the 80 KB let two workgroups share a
 // CU, one computing while the other waits at its barrier.  Bound by the matrix
-// cores and the LDS reads that feed them at 1.0-1.1 PFLOP/s when the tiles fill
-// the chip (eight wavefronts with 256 x 256 tiles, 192 x 256 tiles, and reading
-// the next slice's first operands across the barrier: 1-40 % slower); library
-// and fused times at the layer's sizes stand at the rules in layer_api.cpp.
+// cores and the LDS reads that feed them (3 % of the LDS cycles are bank conflicts)
+// at 0.87-0.95 PFLOP/s where the tiles fill the chip: hidden 1,152, 16,381 tokens, Q,
+// K and V 145 us, W_up with GELU 201, dY1 137 (eight wavefronts with 256 x 256
+// tiles, 192 x 256 tiles, and reading the next slice's first operands across the
+// barrier: 1-40 % slower); library and fused times at the layer's sizes stand at
+// the rules in layer_api.cpp.
 #include <type_traits>
 
 #include "attn_common.h"

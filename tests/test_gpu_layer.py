@@ -1,6 +1,6 @@
-"""GPU parity of the transformer layer (dcp_layer_fwd / dcp_layer_bwd, rocBLAS
-GEMMs around the HIP attention and norm kernels) against the float64 layer
-oracle, and the recomputation contract: a backward that re-runs the forward
+"""GPU parity of the transformer layer (dcp_layer_fwd / dcp_layer_bwd: the HIP
+attention, norm, projection and weight-gradient kernels, the other products in
+rocBLAS) against the float64 layer oracle, and the recomputation contract: a backward that re-runs the forward
 returns bitwise what a backward with the stashed activations returns.
 
 Tolerance: every output, input gradient and weight gradient within 2e-2 of
